@@ -209,7 +209,8 @@ int mlba_plan_destroy(mlba_plan_t plan);
 /* How the blur A and its transpose (or, antireflective model, its reblur
  * A') are computed:
  * MLBA_BLUR_DIRECT (default): LDS-tiled direct convolution, p^2 taps per
- * output; MLBA_BLUR_FFT: circular convolution on an M x M grid, M >= m =
+ * output, with the implicit state on the matrix cores, with the explicit state
+ * and in mlba_apply_A / mlba_residual in the order of the taps; MLBA_BLUR_FFT: circular convolution on an M x M grid, M >= m =
  * n + p - 1, M = 2^a 3^b (section 2.1's FFT evaluation), three passes per
  * product: row transforms, a column pass, inverse row transforms.  For
  * p = 5, 9, 17 and 31 the column pass is the p-tap convolution along y with
@@ -224,10 +225,12 @@ int mlba_plan_destroy(mlba_plan_t plan);
  * mlba_plan_set_blur: MLBA_BLUR_FFT allocates the grid's workspace and PSF
  * spectrum on first use (synchronous) and returns MLBA_EUNSUPPORTED when M
  * would exceed 3072.  mlba_plan_autotune:
- * times both on the plan's own scratch buffers (`reps` calls each, HIP events,
- * synchronous), keeps the faster pair, writes the mean ms per call to ms_out
- * (host, optional: direct A, direct A^T, FFT A, FFT A^T; -1 where unavailable)
- * and returns the chosen mode (>= 0) or an error. */
+ * times them on the plan's own scratch buffers (`reps` calls each, HIP events,
+ * synchronous), keeps the faster pair, for the calls that keep the order of the
+ * taps against that form of the direct blur, writes the mean ms per call to
+ * ms_out (host, optional: direct A, direct A^T on the matrix cores, FFT A, FFT
+ * A^T; -1 where unavailable) and returns the mode chosen against those (>= 0)
+ * or an error. */
 #define MLBA_BLUR_DIRECT 0
 #define MLBA_BLUR_FFT    1
 int mlba_plan_set_blur(mlba_plan_t plan, int mode, hipStream_t stream);
@@ -359,7 +362,8 @@ int mlba_batch_restore(mlba_batch_t batch, const float* const* g, const double* 
  * tunable phase on the batch's own images, `reps` launches each after one
  * untimed launch (HIP events on `stream`, synchronous), and keeps the fastest:
  *   - the blur A and the adjoint blur A^T: one or two output rows per thread
- *     (32- or 64-row tiles; PSFs with p > 33 always use 64-row tiles);
+ *     (32- or 64-row tiles; 16 or 32 rows when some PSF has p > 25) of the
+ *     implicit state (the explicit one has one tile shape);
  *   - the preconditioner's row passes: at most 1, 2 or 4 row pairs per
  *     workgroup, or the built-in choice per size (cap 0);
  *   - its column pass: at most 1, 2, 4, 8 or 16 columns per workgroup, or

@@ -40,7 +40,7 @@ struct mlba_batch_s {
     BatchImage* imgs = nullptr;
     int* maps = nullptr;  // one device buffer holding every map
     size_t maps_cap = 0;  // its size in ints: the largest over every tile choice
-    Map conv_a, conv_at, fold, fill, pre[3], syn[5], ana[5], low[5], shr[5], fill_om;
+    Map conv_a, conv_at, tap_a, tap_at, fold, fill, pre[3], syn[5], ana[5], low[5], shr[5], fill_om;
     // tile choices (set by mlba_batch_autotune)
     int conv_ry[2] = {1, 1};          // output rows per thread of the A and A^T launches
     int rows_want = 0, cols_want = 0;  // transform batching caps (0: built-in choice per size)
@@ -91,7 +91,7 @@ void build_map(const std::vector<int>& tiles, std::vector<int>& host_maps, std::
 int configure(mlba_batch_s* B, hipStream_t s, bool dry_run = false, size_t* ints = nullptr) {
     const int count = B->count;
     int pbase = 0;
-    std::vector<int> pcount(count);
+    std::vector<int> pcount(2 * count);  // residual partials per image: implicit state, explicit state
     for (int i = 0; i < count; ++i) {
         BatchImage& d = B->host[i];
         if (d.precond == MLBA_PRECOND_AR) {  // one row pair per workgroup (the transform is 2(n-1) long)
@@ -104,8 +104,9 @@ int configure(mlba_batch_s* B, hipStream_t s, bool dry_run = false, size_t* ints
             d.fft_cols_shift = fft_seq_shift(d.fft_cols_c);
         }
         d.pbase = pbase;
-        pcount[i] = conv_batched_tiles(d, 1, B->conv_ry[0]);
-        pbase += pcount[i];
+        pcount[i] = conv_batched_tiles(d, 1, B->pmax, B->conv_ry[0]);
+        pcount[count + i] = tapconv_batched_tiles(d, 1);
+        pbase += std::max(pcount[i], pcount[count + i]);
     }
     std::vector<int> hm;
     std::vector<size_t> offs;
@@ -115,10 +116,14 @@ int configure(mlba_batch_s* B, hipStream_t s, bool dry_run = false, size_t* ints
         order.push_back(&m);
     };
     std::vector<int> t(count);
-    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(B->host[i], 1, B->conv_ry[0]);
+    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(B->host[i], 1, B->pmax, B->conv_ry[0]);
     add(B->conv_a, t);
-    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(B->host[i], 0, B->conv_ry[1]);
+    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(B->host[i], 0, B->pmax, B->conv_ry[1]);
     add(B->conv_at, t);
+    for (int i = 0; i < count; ++i) t[i] = tapconv_batched_tiles(B->host[i], 1);
+    add(B->tap_a, t);
+    for (int i = 0; i < count; ++i) t[i] = tapconv_batched_tiles(B->host[i], 0);
+    add(B->tap_at, t);
     for (int i = 0; i < count; ++i) t[i] = B->host[i].bc == MLBA_BC_REFLECT ? B->host[i].n : 0;
     add(B->fold, t);
     for (int planes : {-1, 1}) {  // the explicit state (bands planes), then the implicit one (omega)
@@ -157,7 +162,7 @@ int configure(mlba_batch_s* B, hipStream_t s, bool dry_run = false, size_t* ints
         order[q]->bfirst = B->maps + offs[2 * q + 1];
     }
     HIPCHK(hipMemcpyAsync(B->maps, hm.data(), hm.size() * sizeof(int), hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(B->pcount, pcount.data(), count * sizeof(int), hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(B->pcount, pcount.data(), pcount.size() * sizeof(int), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(B->imgs, B->host.data(), count * sizeof(BatchImage), hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));
     return MLBA_OK;
@@ -210,15 +215,15 @@ int enqueue(mlba_batch_s* B, int iters, bool fill_state, bool implicit, hipStrea
             const Map& m = B->syn[lev];
             HIPCHK(launch_synthesis_batched(I, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 0, s));
         }
-        HIPCHK(launch_conv_batched(I, B->conv_a.bmap, B->conv_a.bfirst, B->conv_a.nblocks, 1, B->pmax, B->partials,
-                                   s, B->conv_ry[0]));
-        HIPCHK(launch_sum_partials_batched(I, B->partials, B->pcount, B->count, k, s));
+        HIPCHK(launch_tapconv_batched(I, B->tap_a.bmap, B->tap_a.bfirst, B->tap_a.nblocks, 1, B->pmax, 0, B->partials,
+                                      s));
+        HIPCHK(launch_sum_partials_batched(I, B->partials, B->pcount + B->count, B->count, k, s));
         if (B->precond != MLBA_PRECOND_NONE)
             for (int pass = 0; pass < 3; ++pass)
                 HIPCHK(launch_precond_batched(I, B->pre[pass].bmap, B->pre[pass].bfirst, B->pre[pass].nblocks, pass,
                                               B->precond, B->nmax, s, B->any_len));
-        HIPCHK(launch_conv_batched(I, B->conv_at.bmap, B->conv_at.bfirst, B->conv_at.nblocks, 0, B->pmax, nullptr,
-                                   s, B->conv_ry[1]));
+        HIPCHK(launch_tapconv_batched(I, B->tap_at.bmap, B->tap_at.bfirst, B->tap_at.nblocks, 0, B->pmax, 0, nullptr,
+                                      s));
         if (B->any_reflect) HIPCHK(launch_fold_batched(I, B->fold.bmap, B->fold.bfirst, B->fold.nblocks, s));
         for (int lev = 1; lev <= B->levels; ++lev) {
             const Map& m = B->ana[lev];
@@ -294,11 +299,12 @@ int mlba_batch_create(mlba_batch_t* batch, int count, const mlba_plan_t* plans, 
         B->nmax = std::max(B->nmax, plans[i]->n);
         if (plans[i]->fd.m > 0) B->any_len = 1;  // a Bluestein-form transform
         B->any_reflect = B->any_reflect || plans[i]->bc == MLBA_BC_REFLECT;
-        pmax_parts += conv_batched_tiles(B->host[i], 1, 1);
     }
+    for (int i = 0; i < count; ++i)
+        pmax_parts += std::max(conv_batched_tiles(B->host[i], 1, B->pmax, 1), tapconv_batched_tiles(B->host[i], 1));
     hipError_t e = hipMalloc(&B->imgs, count * sizeof(BatchImage));
     if (e == hipSuccess) e = hipMalloc(&B->partials, (size_t)std::max(pmax_parts, 1) * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&B->pcount, count * sizeof(int));
+    if (e == hipSuccess) e = hipMalloc(&B->pcount, 2 * count * sizeof(int));
     if (e == hipSuccess) e = hipMalloc(&B->rn, (size_t)count * max_iters * sizeof(double));
     if (e != hipSuccess) {
         mlba_internal_set_hip(e);

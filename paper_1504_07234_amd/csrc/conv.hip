@@ -1,301 +1,428 @@
-// Direct LDS-tiled convolution for the blur A and its transpose A^T
-// (paper section 2: A f is the valid part of the 2-D convolution of the
-// extended image with the PSF; A^T y is the full correlation of y with the
-// PSF, followed for imposed boundaries by the transpose of the padding).
+// Direct convolution for the blur A and its transpose A^T (paper section 2:
+// A f is the valid part of the 2-D convolution of the extended image with the
+// PSF; A^T y is the full correlation of y with the PSF, followed for imposed
+// boundaries by the transpose of the padding), on the matrix cores.
 //
-// One workgroup computes a (32 RY) x 64 output tile.  The (32 RY + p - 1) x
-// (64 + p - 1) input window is staged once in LDS under the requested
-// boundary extension; every thread then owns an RY x 8 block of outputs and
-// walks the p + RY - 1 input rows that feed it: each row segment (8 + p - 1
-// values) is loaded into registers once and applied to every output row it
-// contributes to (RY = 2 halves the LDS reads per FMA).  PSF taps are
-// wavefront-uniform and are read through the scalar cache.  The PSF side is a
-// template parameter for the odd sizes 1..33 (fully unrolled tap loops);
-// larger PSFs use a generic body.
+// Every float32 value x is split into three bfloat16 parts x = x1 + x2 + x3
+// (8 + 8 + 8 significand bits: the sum is x itself), the window's while it is
+// staged, the taps' when the PSF is set.  A product of the blur is then the
+// six products x1 h1, x1 h2, x2 h1, x2 h2, x1 h3, x3 h1 (exact in float32; what
+// is left out is below 2^-25 of |x h|), summed in float32 by
+// v_mfma_f32_16x16x32_bf16: 6 x 16 cycles for the work of 16 x 16 x 32
+// multiply-adds, against 512 cycles of vector FMAs.
 //
-// The tile bodies are device functions shared by the single-image kernels and
-// the batched kernel (one launch covering the tiles of many images), so both
-// paths perform the same arithmetic in the same order.
+// One matrix product: D[m][s] += T_t[m][k] X_t[k][s].  A column s of D is a
+// block of 2 rows x 8 columns of outputs (m = 8 yr + xo), X_t[k][s] the input
+// row t under it from its first column on, and T_t[m][k] = tap(t - yr, k - xo)
+// (zero outside the PSF), so p + 1 products of depth K = 8 + p - 1 (padded to
+// 32 up to p = 25, to 64 up to p = 57) give the 256 outputs of D.  A wave
+// holds R such D's, one below the other: an input row is read from LDS once
+// and used by the R of them through a rolling window of 2 R rows in
+// registers, and the fragments of T_t, laid out in the order of the lanes when
+// the PSF is set, are read from global memory (they stay in the caches) one
+// row ahead.  A workgroup's four waves cover 64 columns x 16 R rows.
+//
+// bfloat16 has float32's exponent range, so nothing is scaled; a window with a
+// value that is not finite in bfloat16 takes the plain tap loop, whose
+// infinities and NaN reach exactly the outputs whose taps touch them.
+//
+// The tile body is a device function shared by the single-image kernels and
+// the batched kernel (one launch covering the tiles of many images); an
+// output's arithmetic does not depend on R or on the tile it lies in.
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace mlba {
 
-constexpr int CONV_TX = 64;  // output columns per workgroup (eight per thread)
-constexpr int CONV_RX = 8;
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <int RY>
-constexpr int conv_ty() { return 32 * RY; }
+constexpr int CONV_TX = 64;     // output columns per workgroup
+constexpr int CONV_SPLITS = 3;  // bfloat16 parts of a float32 value
+constexpr int CONV_K1 = 25;     // largest PSF side whose rows fit one product of depth 32
+constexpr int CONV_PMAX = 49;
 
-__host__ __device__ constexpr int conv_stride(int w) { return ((w + 7) / 8) * 8 + 1; }
+__host__ __device__ constexpr int conv_ty(int r) { return 16 * r; }
+// products of depth 32 per input row
+__host__ __device__ constexpr int conv_depth(int p) { return p <= CONV_K1 ? 1 : 2; }
+// window columns (bfloat16 values) of one part of one row: the last block's K
+__host__ __device__ constexpr int conv_cols(int kc) { return CONV_TX - 8 + 32 * kc; }
+__host__ __device__ constexpr int conv_row_elems(int kc) { return CONV_SPLITS * conv_cols(kc); }
 
-__host__ __device__ constexpr int conv_lds_floats(int p, int ry) {
-    return (32 * ry + p - 1) * conv_stride(CONV_TX + p - 1);
+// rows fetched ahead of the last product, of the window and of the taps
+constexpr int CONV_AHEAD = 3;
+static size_t conv_lds_bytes(int p, int r) {
+    return (size_t)(conv_ty(r) + p - 1 + CONV_AHEAD) * conv_row_elems(conv_depth(p)) * sizeof(__bf16);
 }
 
-int conv_tiles(int D, int ry) { return ((D + CONV_TX - 1) / CONV_TX) * ((D + 32 * ry - 1) / (32 * ry)); }
+// The deepest tile (R row pairs per lane) of a PSF side: R = 4 with the
+// two-product rows would take 66 to 80 KB of LDS.
+static int conv_max_r(int p) { return p <= CONV_K1 ? 4 : 2; }
 
-template <int P, bool FLIP>
-__device__ __forceinline__ float conv_tap(const float* __restrict__ psf, int a, int b) {
-    return FLIP ? psf[(P - 1 - a) * P + (P - 1 - b)] : psf[a * P + b];
+static int conv_tiles_r(int D, int r) {
+    return ((D + CONV_TX - 1) / CONV_TX) * ((D + conv_ty(r) - 1) / conv_ty(r));
 }
 
-__device__ __forceinline__ void conv_stage_window(const ConvJob& j, int P, int TY, int oy0, int ox0,
-                                                  float* tile) {
-    const int TH = TY + P - 1;
-    const int TW = CONV_TX + P - 1;
-    const int LS = conv_stride(TW);
-    for (int i = threadIdx.x; i < TH * TW; i += kBlock) {
-        const int ly = i / TW;
-        const int lx = i - ly * TW;
-        tile[ly * LS + lx] = fetch_ext(j.src, j.S, oy0 + j.org + ly, ox0 + j.org + lx, j.ext);
+// PSF rows a = -1 .. p + CONV_AHEAD (zero outside [0, p))
+size_t conv_taps_elems(int p) { return (size_t)(p + 2 + CONV_AHEAD) * CONV_SPLITS * conv_depth(p) * 32; }
+
+__device__ __forceinline__ void split3(float x, __bf16* h) {
+    h[0] = (__bf16)x;
+    const float r1 = x - (float)h[0];
+    h[1] = (__bf16)r1;
+    h[2] = (__bf16)(r1 - (float)h[1]);
+}
+
+// Fragments for both directions: taps[flip][(((a + 1) S + s) KC + q) 32 + 8 kg
+// + xo] holds tap(a, k - xo), k = 32 q + 8 kg .. + 7; T_t is row a = t in its
+// upper half (yr = 0) and row a = t - 1 in its lower one.
+__global__ __launch_bounds__(64) void conv_taps_kernel(const float* __restrict__ psf, int p, int kc,
+                                                       uint4* __restrict__ taps0, uint4* __restrict__ taps1,
+                                                       double* __restrict__ l1) {
+    if (l1 && blockIdx.x == 0 && blockIdx.y == 0) {  // sum |psf| in index order, for Algorithm 4-NS
+        __shared__ float h[CONV_PMAX * CONV_PMAX];
+        for (int i = threadIdx.x; i < p * p; i += 64) h[i] = fabsf(psf[i]);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double sum = 0.0;
+            for (int i = 0; i < p * p; ++i) sum += (double)h[i];
+            *l1 = sum;
+        }
+    }
+    const int a = (int)blockIdx.x - 1, q = blockIdx.y, flip = threadIdx.x >> 5, l = threadIdx.x & 31;
+    bf16x8 f[CONV_SPLITS];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int b = 32 * q + 8 * (l >> 3) + e - (l & 7);
+        float v = 0.0f;
+        if (a >= 0 && a < p && b >= 0 && b < p) v = psf[flip ? p * p - 1 - (a * p + b) : a * p + b];
+        __bf16 h[CONV_SPLITS];
+        split3(v, h);
+#pragma unroll
+        for (int s = 0; s < CONV_SPLITS; ++s) f[s][e] = h[s];
+    }
+    uint4* out = flip ? taps1 : taps0;
+#pragma unroll
+    for (int s = 0; s < CONV_SPLITS; ++s)
+        out[((size_t)((a + 1) * CONV_SPLITS + s) * kc + q) * 32 + l] = __builtin_bit_cast(uint4, f[s]);
+}
+
+hipError_t launch_conv_taps(const float* psf, int p, uint4* taps0, uint4* taps1, double* l1, hipStream_t s) {
+    const int kc = conv_depth(p);
+    hipLaunchKernelGGL(conv_taps_kernel, dim3(p + 2 + CONV_AHEAD, kc), dim3(64), 0, s, psf, p, kc, taps0, taps1, l1);
+    return hipGetLastError();
+}
+
+struct __attribute__((packed, aligned(4))) FloatQuad {
+    float v[4];
+};
+
+// Source index of position x of an axis under a single-source extension, and
+// whether it has one (zero extension); positions further out than the pad feed
+// no output and are clamped into the image.
+__device__ __forceinline__ int conv_axis(int x, int S, int ext, bool* has) {
+    *has = ext != EXT_ZERO || (x >= 0 && x < S);
+    const bool lo = x < 0, hi = x >= S;
+    const int per = lo ? x + S : (hi ? x - S : x);
+    const int ref = lo ? -1 - x : (hi ? 2 * S - 1 - x : x);
+    const int s = ext == EXT_PERIODIC ? per : ref;
+    return min(max(s, 0), S - 1);
+}
+
+// Splits four values into the rows of the window; chk collects what is left
+// below the second part, which is NaN unless the value is finite in bfloat16.
+template <int C>
+__device__ __forceinline__ void conv_put_split(__bf16* win, const float* v, float* chk) {
+    unsigned w[CONV_SPLITS][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        float r0 = v[2 * e], r1 = v[2 * e + 1];
+#pragma unroll
+        for (int s = 0; s < CONV_SPLITS; ++s) {
+            w[s][e] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
+            if (s + 1 < CONV_SPLITS) {  // the part back as a float: its bits are the upper half
+                r0 -= __builtin_bit_cast(float, w[s][e] << 16);
+                r1 -= __builtin_bit_cast(float, w[s][e] & 0xffff0000u);
+            }
+        }
+        *chk += r0 + r1;
+    }
+#pragma unroll
+    for (int s = 0; s < CONV_SPLITS; ++s) *(uint2*)(win + s * C) = make_uint2(w[s][0], w[s][1]);
+}
+
+// The window of the tile at (oy0, ox0) is rows x conv_cols(KC) values (the
+// columns past the last tap of the last output only have to be finite: their
+// taps are zero).  A thread keeps one group of four columns and takes every
+// eighth row, U in all: conv_fetch issues their loads, conv_commit splits them
+// into LDS.
+template <int KC, int U>
+__device__ __forceinline__ void conv_fetch(const ConvJob& j, int P, int TY, int oy0, int ox0, float (&v)[U][4]) {
+    constexpr int C = conv_cols(KC), RS = kBlock / 32;
+    static_assert(C % 4 == 0 && C / 4 <= 32, "one group of four columns per lane of a half wave");
+    const int rows = TY + P - 1;
+    const int lx = min(4 * ((int)threadIdx.x & 31), C - 4), ly0 = (int)threadIdx.x >> 5;
+    const int S = j.S, ext = j.ext, y0 = oy0 + j.org, x0 = ox0 + j.org;
+    if (y0 >= 0 && x0 >= 0 && y0 + rows <= S && x0 + C <= S) {  // the whole window lies in the image
+        const float* src = j.src + (size_t)(y0 + ly0) * S + x0 + lx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const FloatQuad q = *(const FloatQuad*)(ly0 + u * RS < rows ? src + (size_t)u * RS * S : src);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = q.v[e];
+        }
+    } else if (ext != EXT_ANTIREFLECT) {
+        int xi[4];
+        bool hx[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xi[e] = conv_axis(x0 + lx + e, S, ext, &hx[e]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            bool hy;
+            const float* row = j.src + (size_t)conv_axis(y0 + min(ly0 + u * RS, rows - 1), S, ext, &hy) * S;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float q = row[xi[e]];
+                v[u][e] = hy && hx[e] ? q : 0.0f;
+            }
+        }
     }
 }
 
-// Writes (g - s) or s for the thread's outputs; returns its sum of squares of
-// the written residuals (0 without g).
-template <int RY>
-__device__ __forceinline__ double conv_store(const ConvJob& j, int oy0, int ox0, int ty, int tx0,
-                                             const float (*acc)[CONV_RX]) {
+// Returns whether some value is not finite in bfloat16.  A window that leaves
+// the image under the antireflective extension (up to four sources a value) is
+// read here, row by row.
+template <int KC, int U>
+__device__ __forceinline__ bool conv_commit(const ConvJob& j, int P, int TY, int oy0, int ox0, float (&v)[U][4],
+                                            __bf16* win) {
+    constexpr int C = conv_cols(KC), LS = conv_row_elems(KC), RS = kBlock / 32;
+    const int rows = TY + P - 1;
+    const int lx = 4 * ((int)threadIdx.x & 31), ly0 = (int)threadIdx.x >> 5;
+    const int S = j.S, y0 = oy0 + j.org, x0 = ox0 + j.org;
+    if (lx >= C) return false;
+    float chk = 0.0f;
+    if (j.ext == EXT_ANTIREFLECT && !(y0 >= 0 && x0 >= 0 && y0 + rows <= S && x0 + C <= S)) {
+#pragma unroll 1
+        for (int ly = ly0; ly < rows; ly += RS) {
+            float q[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[e] = fetch_antireflect(j.src, S, y0 + ly, x0 + lx + e);
+            conv_put_split<C>(win + ly * LS + lx, q, &chk);
+        }
+        return chk != chk;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (ly0 + u * RS < rows) conv_put_split<C>(win + (ly0 + u * RS) * LS + lx, v[u], &chk);
+    return chk != chk;
+}
+
+// dst = g - v (returning v's square sum), dst + v or v
+__device__ __forceinline__ double conv_put(const ConvJob& j, int y, int x, float v) {
+    const size_t i = (size_t)y * j.D + x;
     double ss = 0.0;
+    if (j.g) {
+        v = j.g[i] - v;
+        ss = (double)v * (double)v;
+    } else if (j.acc) {
+        v = j.dst[i] + v;
+    }
+    j.dst[i] = v;
+    return ss;
+}
+
+// the same for four columns on 16-byte boundaries
+__device__ __forceinline__ double conv_put4(const ConvJob& j, int y, int x, f32x4 v) {
+    const size_t i = (size_t)y * j.D + x;
+    double ss = 0.0;
+    if (j.g) {
+        v = *(const f32x4*)(j.g + i) - v;
 #pragma unroll
-    for (int h = 0; h < RY; ++h) {
-        const int y = oy0 + RY * ty + h;
+        for (int e = 0; e < 4; ++e) ss += (double)v[e] * (double)v[e];
+    } else if (j.acc) {
+        v = *(const f32x4*)(j.dst + i) + v;
+    }
+    *(f32x4*)(j.dst + i) = v;
+    return ss;
+}
+
+// Plain tap loop over the tile, from global memory.
+__device__ __forceinline__ double conv_tile_taps(const ConvJob& j, int P, int flip, int TY, int oy0, int ox0) {
+    double ss = 0.0;
+    for (int i = threadIdx.x; i < TY * CONV_TX; i += kBlock) {
+        const int y = oy0 + i / CONV_TX, x = ox0 + i % CONV_TX;
+        if (y >= j.D || x >= j.D) continue;
+        float v = 0.0f;
+#pragma unroll 1
+        for (int a = 0; a < P; ++a)
+#pragma unroll 1
+            for (int b = 0; b < P; ++b)
+                v = fmaf(j.psf[flip ? P * P - 1 - (a * P + b) : a * P + b],
+                         fetch_ext(j.src, j.S, y + j.org + a, x + j.org + b, j.ext), v);
+        ss += conv_put(j, y, x, v);
+    }
+    return ss;
+}
+
+// The outputs of the tile whose split window is in LDS.  Returns the thread's
+// sum of squares of the residuals it wrote (0 without g).
+template <int KC, int R>
+__device__ __forceinline__ double conv_products(const ConvJob& j, int P, int oy0, int ox0, const __bf16* win) {
+    constexpr int C = conv_cols(KC), LS = conv_row_elems(KC), S = CONV_SPLITS;
+    constexpr int NF = R == 1 ? 4 : 2 * R;  // rolling window rows
+    constexpr int NT = R == 4 ? 2 : 4;      // rolling tap rows
+    constexpr int UN = NF > NT ? NF : NT;
+    static_assert(NF - 2 * R + 1 <= CONV_AHEAD && NT - 1 <= CONV_AHEAD, "rows fetched ahead");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int seg = lane & 7, rb = (lane >> 3) & 1, kg = lane >> 4;
+    const int row0 = wave * 4 * R + rb * 2 * R;  // the lane's first window (and output) row
+    const __bf16* src = win + row0 * LS + 8 * seg + 8 * kg;
+    const uint4* taps = j.taps;  // uniform; row t of the half waves' lanes below
+    const int depth = KC == 1 ? 1 : conv_depth(P), tstep = S * depth * 32;
+    const int tl = 8 * kg + (lane & 7) + (((lane >> 3) & 1) ? 0 : tstep);
+    f32x4 acc[R], low[R];  // the products x1 h1, and the others
+#pragma unroll
+    for (int i = 0; i < R; ++i) acc[i] = low[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    bf16x8 f[NF][S];  // window rows t .. t + NF - 1, row r in slot r % NF
+    bf16x8 tp[NT][S]; // T_t .. T_{t + NT - 1}
+    auto load_row = [&](bf16x8 (&d)[S], int r) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) d[s] = *(const bf16x8*)(src + r * LS + s * C);
+    };
+    auto load_taps = [&](bf16x8 (&d)[S]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) d[s] = __builtin_bit_cast(bf16x8, taps[s * depth * 32 + tl]);
+        taps += tstep;
+    };
+#pragma unroll 1
+    for (int q = 0; q < depth; ++q) {  // depth 32 at a time: the other half's rows and taps would not fit the registers
+#pragma unroll
+        for (int r = 0; r < NT - 1; ++r) load_taps(tp[r]);
+#pragma unroll
+        for (int r = 0; r < NF - 1; ++r) load_row(f[r], r);
+#pragma unroll 1
+        for (int t0 = 0; t0 <= P; t0 += UN) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int t = t0 + u;
+                if (t > P) break;
+                load_taps(tp[(u + NT - 1) % NT]);
+                load_row(f[(u + NF - 1) % NF], t + NF - 1);
+                __builtin_amdgcn_sched_barrier(0);  // the loads ahead stay ahead of this step's products
+                constexpr int PS[5] = {2, 0, 1, 1, 0}, PT[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tp[u % NT][0], f[(u + 2 * i) % NF][0], acc[i],
+                                                                     0, 0, 0);
+#pragma unroll
+                for (int w = 0; w < 5; ++w)
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+                        low[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tp[u % NT][PT[w]], f[(u + 2 * i) % NF][PS[w]],
+                                                                         low[i], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        src += 32;
+        taps = j.taps + 32;
+    }
+
+    // lane: output block (seg, rb), rows 2 i + (kg >> 1), columns 4 (kg & 1) .. + 3
+    double ss = 0.0;
+    const int x = ox0 + 8 * seg + 4 * (kg & 1);
+    const bool quads = (j.D & 3) == 0 && (((size_t)j.dst | (size_t)j.g) & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int y = oy0 + row0 + 2 * i + (kg >> 1);
         if (y < j.D) {
+            const f32x4 v = acc[i] + low[i];
+            if (quads) {
+                if (x < j.D) ss += conv_put4(j, y, x, v);
+            } else {
 #pragma unroll
-            for (int r = 0; r < CONV_RX; ++r) {
-                const int x = ox0 + tx0 + r;
-                if (x < j.D) {
-                    float v = acc[h][r];
-                    if (j.g) {
-                        v = j.g[(size_t)y * j.D + x] - v;
-                        ss += (double)v * (double)v;
-                    } else if (j.acc) {
-                        v = j.dst[(size_t)y * j.D + x] + v;
-                    }
-                    j.dst[(size_t)y * j.D + x] = v;
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (x + e < j.D) ss += conv_put(j, y, x + e, v[e]);
             }
         }
     }
     return ss;
 }
 
-// One output tile at tile coordinates (bx, by); `tile` is the LDS window.
-template <int P, bool FLIP, int RY>
-__device__ __forceinline__ double conv_tile(const ConvJob& j, int bx, int by, float* tile) {
-    constexpr int TW = CONV_TX + P - 1;
-    constexpr int LS = conv_stride(TW);  // 8k+1 row stride: rows start on distinct banks
-    const int oy0 = by * conv_ty<RY>();
-    const int ox0 = bx * CONV_TX;
-    conv_stage_window(j, P, conv_ty<RY>(), oy0, ox0, tile);
+// One output tile of the job at (oy0, ox0): the thread's sum of squares.
+template <int KC, int R>
+__device__ __forceinline__ double conv_tile(const ConvJob& j, int P, int flip, int oy0, int ox0, __bf16* win) {
+    constexpr int PMAX = KC == 1 ? CONV_K1 : CONV_PMAX;
+    constexpr int U = (conv_ty(R) + PMAX - 1 + 7) / 8;
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = 0;
+    float v[U][4];
+    conv_fetch<KC, U>(j, P, conv_ty(R), oy0, ox0, v);
     __syncthreads();
-
-    // thread: output rows RY*ty .. RY*ty+RY-1, columns tx0 .. tx0+7; input
-    // row RY*ty + q feeds output row RY*ty + h with kernel row q - h
-    const int ty = threadIdx.x >> 3;
-    const int tx0 = (threadIdx.x & 7) * CONV_RX;
-    float acc[RY][CONV_RX];
-#pragma unroll
-    for (int h = 0; h < RY; ++h)
-#pragma unroll
-        for (int r = 0; r < CONV_RX; ++r) acc[h][r] = 0.0f;
-#pragma unroll 1
-    for (int q = 0; q < P + RY - 1; ++q) {
-        const float* row = tile + (RY * ty + q) * LS + tx0;
-        float seg[CONV_RX + P - 1];
-#pragma unroll
-        for (int k = 0; k < CONV_RX + P - 1; ++k) seg[k] = row[k];
-#pragma unroll
-        for (int h = 0; h < RY; ++h) {
-            const int a = q - h;
-            if (a >= 0 && a < P) {
-#pragma unroll
-                for (int b = 0; b < P; ++b) {
-                    const float t = conv_tap<P, FLIP>(j.psf, a, b);
-#pragma unroll
-                    for (int r = 0; r < CONV_RX; ++r) acc[h][r] = fmaf(t, seg[r + b], acc[h][r]);
-                }
-            }
-        }
-    }
-    return conv_store<RY>(j, oy0, ox0, ty, tx0, acc);
-}
-
-// Runtime PSF side, 64-row tile, taps read from LDS after the window.
-__device__ __forceinline__ double conv_tile_generic(const ConvJob& j, int P, int flip, int bx, int by,
-                                                    float* smem) {
-    constexpr int RY = 2;
-    const int TY = conv_ty<RY>();
-    const int LS = conv_stride(CONV_TX + P - 1);
-    float* tile = smem;
-    float* kern = smem + (TY + P - 1) * LS;
-    const int oy0 = by * TY;
-    const int ox0 = bx * CONV_TX;
-    conv_stage_window(j, P, TY, oy0, ox0, tile);
-    for (int i = threadIdx.x; i < P * P; i += kBlock) kern[i] = flip ? j.psf[P * P - 1 - i] : j.psf[i];
+    if (conv_commit<KC, U>(j, P, conv_ty(R), oy0, ox0, v, win)) bad = 1;
     __syncthreads();
-    const int ty = threadIdx.x >> 3;
-    const int tx0 = (threadIdx.x & 7) * CONV_RX;
-    float acc[RY][CONV_RX];
-    for (int h = 0; h < RY; ++h) {
-#pragma unroll
-        for (int r = 0; r < CONV_RX; ++r) acc[h][r] = 0.0f;
-        for (int a = 0; a < P; ++a) {
-            const float* row = tile + (RY * ty + h + a) * LS + tx0;
-            for (int b = 0; b < P; ++b) {
-                const float k = kern[a * P + b];
-#pragma unroll
-                for (int r = 0; r < CONV_RX; ++r) acc[h][r] = fmaf(k, row[r + b], acc[h][r]);
-            }
-        }
-    }
-    return conv_store<RY>(j, oy0, ox0, ty, tx0, acc);
-}
-
-__device__ __forceinline__ void conv_partial(double ss, double* red, double* out) {
-    const double t = block_sum(ss, red);
-    if (threadIdx.x == 0) *out = t;
+    return bad ? conv_tile_taps(j, P, flip, conv_ty(R), oy0, ox0) : conv_products<KC, R>(j, P, oy0, ox0, win);
 }
 
 // ---- single-image kernels -----------------------------------------------
 
-template <int P, bool FLIP, int RY>
-__global__ __launch_bounds__(kBlock) void conv_kernel(ConvJob j, double* __restrict__ partials) {
-    __shared__ float tile[conv_lds_floats(P, RY)];
+template <int KC, int R>
+__global__ __launch_bounds__(kBlock, 3) void conv_kernel(ConvJob j, int P, int flip, double* __restrict__ partials) {
+    extern __shared__ __align__(16) __bf16 conv_win[];
     __shared__ double red[kBlock / 64];
     int bx, by;
     xcd_tile(&bx, &by);
-    const double ss = conv_tile<P, FLIP, RY>(j, bx, by, tile);
-    if (partials) conv_partial(ss, red, partials + blockIdx.y * gridDim.x + blockIdx.x);
+    const double ss = conv_tile<KC, R>(j, P, flip, by * conv_ty(R), bx * CONV_TX, conv_win);
+    if (partials) {
+        const double t = block_sum(ss, red);
+        if (threadIdx.x == 0) partials[blockIdx.y * gridDim.x + blockIdx.x] = t;
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void conv_kernel_generic(ConvJob j, int P, int flip,
-                                                              double* __restrict__ partials) {
-    extern __shared__ float smem[];
-    __shared__ double red[kBlock / 64];
-    int bx, by;
-    xcd_tile(&bx, &by);
-    const double ss = conv_tile_generic(j, P, flip, bx, by, smem);
-    if (partials) conv_partial(ss, red, partials + blockIdx.y * gridDim.x + blockIdx.x);
+// Row pairs per lane of a D x D output: the deepest tile that still gives the
+// chip two workgroups per CU.
+static int conv_default_r(int D, int p) {
+    int r = conv_max_r(p);
+    while (r > 1 && conv_tiles_r(D, r) < 512) r /= 2;
+    return r;
 }
 
-// Output-tile height: two rows per thread (fewer LDS reads per FMA) unless
-// the 64-row tiling leaves a nearly empty second round of workgroups, in
-// which case one row per thread (32-row tiles) balances better.
-int conv_default_rows(int D, int p) {
-    const long t2 = conv_tiles(D, 2);
-    const int lds2 = conv_lds_floats(p, 2) * 4;
-    const long slots = 256L * (160 * 1024 / lds2);
-    const long rounds = (t2 + slots - 1) / slots;
-    const double fill = (double)t2 / (double)(rounds * slots);
-    return fill >= 0.75 ? 2 : 1;
-}
+int conv_partials_count(int D) { return conv_tiles_r(D, 1); }  // upper bound over the tilings
 
-int conv_partials_count(int D) { return conv_tiles(D, 1); }  // upper bound over both tilings
-
-template <int P, int RY>
-static hipError_t launch_fixed_ry(const ConvJob& j, int flip, double* partials, int* n_partials, hipStream_t s) {
-    dim3 grid((j.D + CONV_TX - 1) / CONV_TX, (j.D + conv_ty<RY>() - 1) / conv_ty<RY>());
+template <int KC, int R>
+static hipError_t launch_cr(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s) {
+    dim3 grid((j.D + CONV_TX - 1) / CONV_TX, (j.D + conv_ty(R) - 1) / conv_ty(R));
     if (n_partials) *n_partials = (int)(grid.x * grid.y);
-    if (flip)
-        hipLaunchKernelGGL((conv_kernel<P, true, RY>), grid, dim3(kBlock), 0, s, j, partials);
-    else
-        hipLaunchKernelGGL((conv_kernel<P, false, RY>), grid, dim3(kBlock), 0, s, j, partials);
+    hipLaunchKernelGGL((conv_kernel<KC, R>), grid, dim3(kBlock), conv_lds_bytes(p, R), s, j, p, flip, partials);
     return hipGetLastError();
 }
 
-template <int P>
-static hipError_t launch_fixed(const ConvJob& j, int flip, int ry, double* partials, int* n_partials,
-                               hipStream_t s) {
-    if (ry != 1 && ry != 2) ry = conv_default_rows(j.D, P);
-    if (ry == 2) return launch_fixed_ry<P, 2>(j, flip, partials, n_partials, s);
-    return launch_fixed_ry<P, 1>(j, flip, partials, n_partials, s);
-}
-
-static size_t conv_generic_lds(int p) { return (size_t)(conv_lds_floats(p, 2) + p * p) * sizeof(float); }
-
-hipError_t launch_conv_job(const ConvJob& j, int p, int flip, int ry, double* partials, int* n_partials,
-                           hipStream_t s) {
-    switch (p) {
-#define MLBA_CONV_CASE(PP) \
-    case PP:               \
-        return launch_fixed<PP>(j, flip, ry, partials, n_partials, s);
-        MLBA_CONV_CASE(1)
-        MLBA_CONV_CASE(3)
-        MLBA_CONV_CASE(5)
-        MLBA_CONV_CASE(7)
-        MLBA_CONV_CASE(9)
-        MLBA_CONV_CASE(11)
-        MLBA_CONV_CASE(13)
-        MLBA_CONV_CASE(15)
-        MLBA_CONV_CASE(17)
-        MLBA_CONV_CASE(19)
-        MLBA_CONV_CASE(21)
-        MLBA_CONV_CASE(23)
-        MLBA_CONV_CASE(25)
-        MLBA_CONV_CASE(27)
-        MLBA_CONV_CASE(29)
-        MLBA_CONV_CASE(31)
-        MLBA_CONV_CASE(33)
-#undef MLBA_CONV_CASE
-        default: {
-            constexpr int TY = conv_ty<2>();
-            dim3 grid((j.D + CONV_TX - 1) / CONV_TX, (j.D + TY - 1) / TY);
-            if (n_partials) *n_partials = (int)(grid.x * grid.y);
-            const size_t lds = conv_generic_lds(p);
-            if (lds > 64 * 1024) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(conv_kernel_generic, grid, dim3(kBlock), lds, s, j, p, flip, partials);
-            return hipGetLastError();
-        }
+hipError_t launch_conv_job(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s) {
+    if (p < 1 || p > CONV_PMAX || !j.taps) return hipErrorInvalidValue;
+    const int r = conv_default_r(j.D, p);
+    if (conv_depth(p) == 1) {
+        if (r == 4) return launch_cr<1, 4>(j, p, flip, partials, n_partials, s);
+        if (r == 2) return launch_cr<1, 2>(j, p, flip, partials, n_partials, s);
+        return launch_cr<1, 1>(j, p, flip, partials, n_partials, s);
     }
+    if (r == 2) return launch_cr<2, 2>(j, p, flip, partials, n_partials, s);
+    return launch_cr<2, 1>(j, p, flip, partials, n_partials, s);
 }
 
 // ---- batched kernel: tiles of many images in one launch ------------------
-// Workgroup b serves image bmap[b], local tile b - bfirst[image].  Images with
-// p <= 33 use one-row-per-thread tiles, larger PSFs the generic 64-row body.
+// Workgroup b serves image bmap[b], local tile b - bfirst[image].
 // FLIP: r = g - A u with the residual-norm partial of the tile written to
-// partials[pbase + local tile]; otherwise the A^T correlation.
+// partials[pbase + local tile]; otherwise the A^T correlation.  An image of
+// smaller PSF side than the launch's widest runs in the same window.
 
-template <bool FLIP, int RY>
-__device__ __forceinline__ double conv_tile_dispatch(const ConvJob& j, int p, int bx, int by, float* lds) {
-    switch (p) {
-#define MLBA_CONV_DISPATCH(PP) \
-    case PP:                   \
-        return conv_tile<PP, FLIP, RY>(j, bx, by, lds);
-        MLBA_CONV_DISPATCH(1)
-        MLBA_CONV_DISPATCH(3)
-        MLBA_CONV_DISPATCH(5)
-        MLBA_CONV_DISPATCH(7)
-        MLBA_CONV_DISPATCH(9)
-        MLBA_CONV_DISPATCH(11)
-        MLBA_CONV_DISPATCH(13)
-        MLBA_CONV_DISPATCH(15)
-        MLBA_CONV_DISPATCH(17)
-        MLBA_CONV_DISPATCH(19)
-        MLBA_CONV_DISPATCH(21)
-        MLBA_CONV_DISPATCH(23)
-        MLBA_CONV_DISPATCH(25)
-        MLBA_CONV_DISPATCH(27)
-        MLBA_CONV_DISPATCH(29)
-        MLBA_CONV_DISPATCH(31)
-        MLBA_CONV_DISPATCH(33)
-#undef MLBA_CONV_DISPATCH
-        default:
-            return conv_tile_generic(j, p, FLIP ? 1 : 0, bx, by, lds);
-    }
-}
-
-// rows per thread of an image's tiles: the launch's choice, or the generic
-// body's 64-row tiles for p > 33
-static int batched_rows(int p, int ry) { return p > 33 ? 2 : ry; }
-
-template <bool FLIP, int RY>
-__global__ __launch_bounds__(kBlock) void conv_batched_kernel(const BatchImage* __restrict__ imgs,
-                                                              const int* __restrict__ bmap,
-                                                              const int* __restrict__ bfirst,
-                                                              double* __restrict__ partials) {
-    extern __shared__ float smem[];
+template <bool FLIP, int KC, int R>
+__global__ __launch_bounds__(kBlock, 3) void conv_batched_kernel(const BatchImage* __restrict__ imgs,
+                                                                 const int* __restrict__ bmap,
+                                                                 const int* __restrict__ bfirst,
+                                                                 double* __restrict__ partials) {
+    extern __shared__ __align__(16) __bf16 conv_win[];
     __shared__ double red[kBlock / 64];
     const int im = bmap[blockIdx.x];
     const BatchImage& I = imgs[im];
@@ -303,40 +430,46 @@ __global__ __launch_bounds__(kBlock) void conv_batched_kernel(const BatchImage* 
     const int local = blockIdx.x - bfirst[im];
     const int gx = (j.D + CONV_TX - 1) / CONV_TX;
     const int by = local / gx;
-    const int bx = local - by * gx;
-    const double ss = conv_tile_dispatch<FLIP, RY>(j, I.p, bx, by, smem);
-    if (FLIP && partials) conv_partial(ss, red, partials + I.pbase + local);
+    const double ss = conv_tile<KC, R>(j, I.p, FLIP, by * conv_ty(R), (local - by * gx) * CONV_TX, conv_win);
+    if (FLIP && partials) {
+        const double t = block_sum(ss, red);
+        if (threadIdx.x == 0) partials[I.pbase + local] = t;
+    }
 }
 
-int conv_batched_tiles(const BatchImage& I, int flip, int ry) {
+// row pairs per lane of a launch's tiles (32 or 64 rows, half of it with the
+// two-product rows)
+static int batched_r(int pmax, int ry) { return pmax <= CONV_K1 ? 2 * ry : ry; }
+
+int conv_batched_tiles(const BatchImage& I, int flip, int pmax, int ry) {
     const ConvJob j = flip ? blur_job(I) : blurT_job(I);
-    return conv_tiles(j.D, batched_rows(I.p, ry));
+    return conv_tiles_r(j.D, batched_r(pmax, ry));
 }
 
-static size_t conv_batched_lds(int pmax, int ry) {
-    const size_t fixed = (size_t)conv_lds_floats(pmax < 33 ? pmax : 33, ry) * sizeof(float);
-    if (pmax <= 33) return fixed;
-    const size_t gen = conv_generic_lds(pmax);
-    return gen > fixed ? gen : fixed;
-}
-
-template <bool FLIP, int RY>
-static hipError_t launch_cb(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int pmax,
+template <bool FLIP, int KC, int R>
+static hipError_t launch_cb(const BatchImage* imgs, const int* bmap, const int* bfirst, int tiles, int pmax,
                             double* partials, hipStream_t s) {
-    const size_t lds = conv_batched_lds(pmax, RY);
-    if (lds > 64 * 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((conv_batched_kernel<FLIP, RY>), dim3(nblocks), dim3(kBlock), lds, s, imgs, bmap, bfirst,
-                       partials);
+    hipLaunchKernelGGL((conv_batched_kernel<FLIP, KC, R>), dim3(tiles), dim3(kBlock), conv_lds_bytes(pmax, R), s,
+                       imgs, bmap, bfirst, partials);
     return hipGetLastError();
+}
+
+template <bool FLIP>
+static hipError_t launch_cbf(const BatchImage* imgs, const int* bmap, const int* bfirst, int tiles, int pmax,
+                             double* partials, hipStream_t s, int ry) {
+    const int r = batched_r(pmax, ry);
+    if (pmax > CONV_K1) return r == 2 ? launch_cb<FLIP, 2, 2>(imgs, bmap, bfirst, tiles, pmax, partials, s)
+                                      : launch_cb<FLIP, 2, 1>(imgs, bmap, bfirst, tiles, pmax, partials, s);
+    return r == 4 ? launch_cb<FLIP, 1, 4>(imgs, bmap, bfirst, tiles, pmax, partials, s)
+                  : launch_cb<FLIP, 1, 2>(imgs, bmap, bfirst, tiles, pmax, partials, s);
 }
 
 hipError_t launch_conv_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int flip,
                                int pmax, double* partials, hipStream_t s, int ry) {
     if (nblocks <= 0) return hipSuccess;
-    if (flip) return ry == 2 ? launch_cb<true, 2>(imgs, bmap, bfirst, nblocks, pmax, partials, s)
-                             : launch_cb<true, 1>(imgs, bmap, bfirst, nblocks, pmax, partials, s);
-    return ry == 2 ? launch_cb<false, 2>(imgs, bmap, bfirst, nblocks, pmax, nullptr, s)
-                   : launch_cb<false, 1>(imgs, bmap, bfirst, nblocks, pmax, nullptr, s);
+    if (pmax > CONV_PMAX) return hipErrorInvalidValue;
+    return flip ? launch_cbf<true>(imgs, bmap, bfirst, nblocks, pmax, partials, s, ry)
+                : launch_cbf<false>(imgs, bmap, bfirst, nblocks, pmax, nullptr, s, ry);
 }
 
 // ---- transpose of the reflective padding ---------------------------------

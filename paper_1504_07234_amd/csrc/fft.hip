@@ -853,13 +853,6 @@ __device__ __forceinline__ void ns_init(double* st, double a, double rn_sq, doub
     st[3] = qn;
 }
 
-// sum |psf| in index order (one thread), for the bracket of every iteration
-__global__ void ns_psf_l1_kernel(const float* __restrict__ psf, int p, double* __restrict__ state) {
-    double l1 = 0.0;
-    for (int i = 0; i < p * p; ++i) l1 += fabs((double)psf[i]);
-    state[NS_L1] = l1;
-}
-
 // The sums S0, S1, R of one step's NS_BLOCKS x 3 partials, in one fixed
 // order (the same in every workgroup that forms them); all threads call.
 __device__ __forceinline__ void ns_sums(const double* __restrict__ part, double (*red)[kBlock / 64], double* S) {
@@ -1019,7 +1012,7 @@ __global__ __launch_bounds__(kBlock) void ns_final_kernel(double* __restrict__ s
 }
 
 // `steps` Newton steps (steps + 1 launches); state: the 24-double buffer
-// above (sum |psf| set by launch_ns_psf_l1), part: 2 x 3 NS_BLOCKS doubles.
+// above (sum |psf| in slot ns_l1_slot(), set by launch_conv_taps), part: 2 x 3 NS_BLOCKS doubles.
 hipError_t launch_ns_alpha(const void* T, int real, int n, int ts, const float* spec, double* state, double* part,
                            const double* rn_sq, double noise, double q, double rho, double alpha_first, int first,
                            int steps, double* hist, hipStream_t s) {
@@ -1037,13 +1030,9 @@ hipError_t launch_ns_alpha(const void* T, int real, int n, int ts, const float* 
     return hipGetLastError();
 }
 
-hipError_t launch_ns_psf_l1(const float* psf, int p, double* state, hipStream_t s) {
-    hipLaunchKernelGGL(ns_psf_l1_kernel, dim3(1), dim3(1), 0, s, psf, p, state);
-    return hipGetLastError();
-}
-
 int ns_partials_needed() { return 2 * 3 * NS_BLOCKS; }
 int ns_state_doubles() { return 24; }
+int ns_l1_slot() { return NS_L1; }
 int ns_alpha_launches(int steps) { return steps + 1; }
 
 // ---------------------------------------------------------------------------

@@ -55,6 +55,7 @@ struct ConvJob {
     int D;
     const float* g;
     const float* psf;
+    const uint4* taps;  // the split taps' fragments of this direction (launch_conv_taps)
     int acc;
 };
 
@@ -78,6 +79,7 @@ struct BatchImage {
     float* tmp0;
     float* tmp1;
     const float* psf;
+    const uint4* taps[2];  // split taps: [0] A^T, [1] A (launch_conv_taps)
     const float* spec;
     void* swork;
     const float2* tw;
@@ -118,6 +120,7 @@ __host__ __device__ inline ConvJob blur_job(const BatchImage& I) {
     j.D = I.n;
     j.g = I.g;
     j.psf = I.psf;
+    j.taps = I.taps[1];
     j.acc = 0;
     return j;
 }
@@ -133,6 +136,7 @@ __host__ __device__ inline ConvJob blurT_job(const BatchImage& I) {
     j.S = I.n;
     j.g = nullptr;
     j.psf = I.psf;
+    j.taps = I.taps[0];
     j.acc = 0;
     if (I.bc == 0 || I.bc == 1) {
         j.ext = EXT_ZERO;
@@ -154,18 +158,25 @@ __host__ __device__ inline ConvJob blurT_job(const BatchImage& I) {
 // with K = H rotated by 180 degrees (flip = 1, the blur A) or K = H
 // (flip = 0, the correlation of A^T).  src is S x S, dst is D x D.
 // partials (optional, needs g): one double per workgroup with sum of dst^2.
-hipError_t launch_conv(const float* src, int S, int ext, int org, float* dst, int D,
-                       const float* g, const float* psf, int p, int flip, double* partials,
-                       int* n_partials, hipStream_t s);
-// ry: output rows per thread (1 or 2; other values pick by occupancy)
-hipError_t launch_conv_job(const ConvJob& j, int p, int flip, int ry, double* partials, int* n_partials,
-                           hipStream_t s);
+hipError_t launch_conv_job(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s);
 int conv_partials_count(int D);
-int conv_default_rows(int D, int p);
-int conv_tiles(int D, int ry);
+// the taps of both directions split into bfloat16 parts in the order of the
+// matrix fragments, conv_taps_elems(p) values each: taps0 for A^T, taps1 for A;
+// l1 (a device double or null): sum |psf|
+size_t conv_taps_elems(int p);
+hipError_t launch_conv_taps(const float* psf, int p, uint4* taps0, uint4* taps1, double* l1, hipStream_t s);
+// the same jobs (without accumulation) in the order of the taps on the vector
+// units, for the results that hang on it (tapconv.hip); batched: the tiles of
+// every image in one launch, same_p: every image's PSF side is pmax
+hipError_t launch_tapconv(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s);
+int tapconv_partials_count(int D);
+int tapconv_batched_tiles(const BatchImage& I, int flip);
+hipError_t launch_tapconv_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int flip,
+                                  int pmax, int same_p, double* partials, hipStream_t s);
 // batched: tiles of every image in one launch (flip = 1: residual, 0: A^T);
-// ry = output rows per thread (1 or 2) of the images with p <= 33
-int conv_batched_tiles(const BatchImage& I, int flip, int ry = 1);
+// ry = 1 or 2: tiles of 32 or 64 rows (16 or 32 when pmax, the widest PSF of
+// the batch, is over 25)
+int conv_batched_tiles(const BatchImage& I, int flip, int pmax, int ry = 1);
 hipError_t launch_conv_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
                                int flip, int pmax, double* partials, hipStream_t s, int ry = 1);
 hipError_t launch_fold_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
@@ -359,15 +370,15 @@ hipError_t launch_pcg_check_sum(double* st, const double* part, int np, double* 
                                 double tol, int* hist, hipStream_t s);
 // Algorithm 4-NS: alpha_n on the device from the BCCB half spectrum T
 // (float2, real = 0) or the DCT coefficients (float, real = 1); state:
-// ns_state_doubles() device doubles (launch_ns_psf_l1 after every PSF
-// change), alpha_n at state[0]; hist: a device double or null; part: at
+// ns_state_doubles() device doubles (sum |psf| in
+// slot ns_l1_slot(), from launch_conv_taps), alpha_n at state[0]; hist: a device double or null; part: at
 // least ns_partials_needed() device doubles
 hipError_t launch_ns_alpha(const void* T, int real, int n, int ts, const float* spec, double* state, double* part,
                            const double* rn_sq, double noise, double q, double rho, double alpha_first, int first,
                            int steps, double* hist, hipStream_t s);
-hipError_t launch_ns_psf_l1(const float* psf, int p, double* state, hipStream_t s);
 int ns_partials_needed();
 int ns_state_doubles();
+int ns_l1_slot();
 int ns_alpha_launches(int steps);  // kernels launch_ns_alpha enqueues
 // columns: forward FFT, write spec = |.|^2 (same transposed layout)
 hipError_t launch_fft_cols_power(const float2* T, int n, int ts, float* spec, const FftDesc& fd,

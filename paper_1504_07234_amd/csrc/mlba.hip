@@ -177,6 +177,8 @@ void free_plan(mlba_plan_s* P) {
     delete P;
 }
 
+bool uses_fft(const mlba_plan_s* P, bool taps) { return taps ? P->blur_fft_taps : P->blur_fft; }
+
 size_t NN(const mlba_plan_s* P) { return (size_t)P->N * P->N; }
 
 // r = g - A u (g may be null: y = A u); partial sums of r^2 into P->partials
@@ -203,9 +205,11 @@ int blur_grid_forward(mlba_plan_s* P, const float* u, hipStream_t s) {
     return MLBA_OK;
 }
 
-int do_blur(mlba_plan_s* P, const float* u, const float* g, float* y, bool want_norm, int* nparts,
+// (taps: a call that keeps the order of the taps, see tapconv.hip, with the
+// blur chosen for those)
+int do_blur(mlba_plan_s* P, const float* u, const float* g, float* y, bool want_norm, int* nparts, bool taps,
             hipStream_t s) {
-    if (P->blur_fft) {
+    if (uses_fft(P, taps)) {
         const int n = P->n, p = P->p;
         STCHK(blur_grid_forward(P, u, s));
         HIPCHK(launch_fc_rows_inv(P->fc, p - 1, p - 1, n, y, g, 0, g && want_norm ? P->partials : nullptr, nparts,
@@ -217,7 +221,9 @@ int do_blur(mlba_plan_s* P, const float* u, const float* g, float* y, bool want_
     d.u = const_cast<float*>(u);
     d.g = g;
     d.r = y;
-    HIPCHK(launch_conv_job(blur_job(d), P->p, 1, P->conv_rows[0], want_norm ? P->partials : nullptr, nparts, s));
+    double* part = want_norm ? P->partials : nullptr;
+    if (taps) HIPCHK(launch_tapconv(blur_job(d), P->p, 1, part, nparts, s));
+    else HIPCHK(launch_conv_job(blur_job(d), P->p, 1, part, nparts, s));
     MARK(BLUR, CONV_BLUR);
     return MLBA_OK;
 }
@@ -237,16 +243,16 @@ PrecondRows precond_rows(const mlba_plan_s* P) {
 // FFT blur with the BCCB or DCT preconditioner: the residual's inverse row
 // pass and the preconditioner's forward row pass run as one launch (as do the
 // preconditioner's inverse row pass and the forward row pass of A^T).
-bool fused_fft_path(const mlba_plan_s* P) {
-    return P->blur_fft && P->bc != MLBA_BC_ANTIREFLECT &&
+bool fused_fft_path(const mlba_plan_s* P, bool taps) {
+    return uses_fft(P, taps) && P->bc != MLBA_BC_ANTIREFLECT &&
            (P->precond == MLBA_PRECOND_BCCB || P->precond == MLBA_PRECOND_DCT) &&
            fftconv_fusable(P->fc, P->n, precond_rows(P));
 }
 
 // FFT blur of the antireflective model with the antireflective transform: the
 // residual's inverse row pass runs with the transform's forward row pass.
-bool fused_ar_path(const mlba_plan_s* P) {
-    return P->blur_fft && P->bc == MLBA_BC_ANTIREFLECT && P->precond == MLBA_PRECOND_AR &&
+bool fused_ar_path(const mlba_plan_s* P, bool taps) {
+    return uses_fft(P, taps) && P->bc == MLBA_BC_ANTIREFLECT && P->precond == MLBA_PRECOND_AR &&
            fftconv_ar_fusable(P->fc, P->n, P->fd);
 }
 
@@ -308,12 +314,13 @@ int do_blurT_fft(mlba_plan_s* P, const float* y, float* w, int accum, hipStream_
     return blurT_grid_finish(P, w, accum, s);
 }
 
-int do_blurT(mlba_plan_s* P, const float* y, float* w, hipStream_t s) {
-    if (P->blur_fft) return do_blurT_fft(P, y, w, 0, s);
+int do_blurT(mlba_plan_s* P, const float* y, float* w, hipStream_t s, bool taps = false) {
+    if (uses_fft(P, taps)) return do_blurT_fft(P, y, w, 0, s);
     BatchImage d = plan_desc(P);
     d.t = const_cast<float*>(y);
     d.w = w;
-    HIPCHK(launch_conv_job(blurT_job(d), P->p, 0, P->conv_rows[1], nullptr, nullptr, s));
+    if (taps) HIPCHK(launch_tapconv(blurT_job(d), P->p, 0, nullptr, nullptr, s));
+    else HIPCHK(launch_conv_job(blurT_job(d), P->p, 0, nullptr, nullptr, s));
     MARK(BLUR_T, CONV_BLUR_T);
     if (P->bc == MLBA_BC_REFLECT) {
         HIPCHK(launch_fold_reflect(P->wext, P->n + P->p - 1, w, P->n, P->c, s));
@@ -522,7 +529,7 @@ int do_blurT_acc(mlba_plan_s* P, const float* y, float* omega, hipStream_t s) {
     ConvJob j = blurT_job(d);
     const bool fold = P->bc == MLBA_BC_REFLECT;
     j.acc = fold ? 0 : 1;
-    HIPCHK(launch_conv_job(j, P->p, 0, P->conv_rows[1], nullptr, nullptr, s));
+    HIPCHK(launch_conv_job(j, P->p, 0, nullptr, nullptr, s));
     MARK(BLUR_T, CONV_BLUR_T);
     if (fold) {
         HIPCHK(launch_fold_reflect(P->wext, P->n + P->p - 1, omega, P->n, P->c, s, 1));
@@ -564,7 +571,7 @@ int do_gram(mlba_plan_s* P, float* d, float* q, double alpha, int* np, const Pcg
         return MLBA_OK;
     }
     STCHK(do_blurT(P, d, P->w, s));
-    STCHK(do_blur(P, P->w, nullptr, q, false, nullptr, s));
+    STCHK(do_blur(P, P->w, nullptr, q, false, nullptr, false, s));
     HIPCHK(launch_axpy(q, d, nn, (float)alpha, s));
     HIPCHK(launch_dot_partials(d, q, nn, P->partials, np, s));
     return MLBA_OK;
@@ -575,7 +582,7 @@ int do_gram(mlba_plan_s* P, float* d, float* q, double alpha, int* np, const Pcg
 bool pcg_fused_rows(const mlba_plan_s* P) {
     return P->precond == MLBA_PRECOND_BCCB && pcg_rows_c2r_partials(P->n) <= P->partials_cap;
 }
-bool pcg_fused_start(const mlba_plan_s* P) { return pcg_fused_rows(P) && fused_fft_path(P); }
+bool pcg_fused_start(const mlba_plan_s* P) { return pcg_fused_rows(P) && fused_fft_path(P, false); }
 
 // rows_ready: P's forward row pass of res is already in the plan's workspace
 int do_pcg(mlba_plan_s* P, double alpha, int max_steps, double tol, int* hist, bool rows_ready, hipStream_t s) {
@@ -651,7 +658,7 @@ namespace {
 
 // y = A^T P_alpha A v (A' P_alpha A for antireflective conditions)
 int normal_matvec(mlba_plan_s* P, const float* v, float* y, double alpha, hipStream_t s) {
-    STCHK(do_blur(P, v, nullptr, P->r, false, nullptr, s));
+    STCHK(do_blur(P, v, nullptr, P->r, false, nullptr, false, s));
     STCHK(do_precond(P, P->r, P->t, alpha, s));
     return do_blurT(P, P->t, y, s);
 }
@@ -865,6 +872,7 @@ int mlba_plan_create(mlba_plan_t* plan, int n, int p, int bc, int precond, int l
     const size_t nn = (size_t)N * N, obs = (size_t)n * n;
     const int m = n + p - 1;
     P->partials_cap = conv_partials_count(n);
+    if (P->partials_cap < tapconv_partials_count(n)) P->partials_cap = tapconv_partials_count(n);
     if (P->partials_cap < reduce_partials_cap()) P->partials_cap = reduce_partials_cap();
     if (P->partials_cap < ns_partials_needed()) P->partials_cap = ns_partials_needed();
     P->rn_cap = 1 << 16;
@@ -877,6 +885,8 @@ int mlba_plan_create(mlba_plan_t* plan, int n, int p, int bc, int precond, int l
         }                                                  \
     } while (0)
     ALLOC(P->psf, (size_t)p * p);
+    ALLOC(P->taps[0], 2 * conv_taps_elems(p));
+    P->taps[1] = P->taps[0] + conv_taps_elems(p);
     ALLOC(P->u, nn);
     ALLOC(P->r, obs);
     ALLOC(P->t, obs);
@@ -978,8 +988,8 @@ int mlba_plan_create(mlba_plan_t* plan, int n, int p, int bc, int precond, int l
 int mlba_plan_set_psf(mlba_plan_t P, const float* psf, hipStream_t s) {
     if (!P || !psf) return MLBA_EINVAL;
     HIPCHK(hipMemcpyAsync(P->psf, psf, (size_t)P->p * P->p * sizeof(float), hipMemcpyDeviceToDevice, s));
+    HIPCHK(launch_conv_taps(P->psf, P->p, P->taps[0], P->taps[1], P->ns ? P->ns + ns_l1_slot() : nullptr, s));
     if (P->fc.H) HIPCHK(launch_fftconv_spectrum(P->fc, P->psf, P->p, s));
-    if (P->ns) HIPCHK(launch_ns_psf_l1(P->psf, P->p, P->ns, s));
     return note_work(P, compute_spectrum(P, s), s);
 }
 
@@ -1069,27 +1079,35 @@ extern "C" {
 int mlba_plan_set_blur(mlba_plan_t P, int mode, hipStream_t s) {
     if (!P || mode < MLBA_BLUR_DIRECT || mode > MLBA_BLUR_FFT) return MLBA_EINVAL;
     if (mode == MLBA_BLUR_FFT) STCHK(ensure_fftconv(P, s));
-    P->blur_fft = mode == MLBA_BLUR_FFT ? 1 : 0;
+    P->blur_fft = P->blur_fft_taps = mode == MLBA_BLUR_FFT ? 1 : 0;
     return MLBA_OK;
 }
 
 int mlba_plan_autotune(mlba_plan_t P, int reps, double* ms_out, hipStream_t s) {
     if (!P || reps < 1) return MLBA_EINVAL;
-    double t[2][2] = {{0.0, 0.0}, {-1.0, -1.0}};  // [direct / fft][A / A^T]
-    const int keep = P->blur_fft;
+    // [direct / fft / direct in the order of the taps][A / A^T]
+    double t[3][2] = {{0.0, 0.0}, {-1.0, -1.0}, {0.0, 0.0}};
+    const int keep[2] = {P->blur_fft, P->blur_fft_taps};
     const int have_fft = ensure_fftconv(P, s);
     if (have_fft < 0 && have_fft != MLBA_EUNSUPPORTED) return have_fft;
-    for (int mode = 0; mode < (have_fft == MLBA_OK ? 2 : 1); ++mode) {
-        P->blur_fft = mode;
+    for (int mode = 0; mode < 3; ++mode) {
+        if (mode == 1 && have_fft != MLBA_OK) continue;
+        const bool taps = mode == 2;
+        P->blur_fft = mode == 1;
+        P->blur_fft_taps = 0;
         // scratch only: u -> r and t -> w of the plan
-        int st = time_ms([&]() { return do_blur(P, P->u, nullptr, P->r, false, nullptr, s); }, reps, s, &t[mode][0]);
-        if (st >= 0) st = time_ms([&]() { return do_blurT(P, P->t, P->w, s); }, reps, s, &t[mode][1]);
+        int st = time_ms([&]() { return do_blur(P, P->u, nullptr, P->r, false, nullptr, taps, s); }, reps, s,
+                         &t[mode][0]);
+        if (st >= 0) st = time_ms([&]() { return do_blurT(P, P->t, P->w, s, taps); }, reps, s, &t[mode][1]);
         if (st < 0) {
-            P->blur_fft = keep;
+            P->blur_fft = keep[0];
+            P->blur_fft_taps = keep[1];
             return st;
         }
     }
-    P->blur_fft = (have_fft == MLBA_OK && t[1][0] + t[1][1] < t[0][0] + t[0][1]) ? 1 : 0;
+    const double fft = have_fft == MLBA_OK ? t[1][0] + t[1][1] : 1e300;
+    P->blur_fft = fft < t[0][0] + t[0][1] ? 1 : 0;
+    P->blur_fft_taps = fft < t[2][0] + t[2][1] ? 1 : 0;
     if (ms_out)
         for (int i = 0; i < 4; ++i) ms_out[i] = t[i / 2][i % 2];
     return P->blur_fft ? MLBA_BLUR_FFT : MLBA_BLUR_DIRECT;
@@ -1118,12 +1136,12 @@ int mlba_plan_opnorm(mlba_plan_t P, double alpha, int iters, double* out, hipStr
 
 int mlba_apply_A(mlba_plan_t P, const float* u, float* y, hipStream_t s) {
     if (!P || !u || !y) return MLBA_EINVAL;
-    return note_work(P, do_blur(P, u, nullptr, y, false, nullptr, s), s);
+    return note_work(P, do_blur(P, u, nullptr, y, false, nullptr, true, s), s);
 }
 
 int mlba_residual(mlba_plan_t P, const float* g, const float* u, float* r, hipStream_t s) {
     if (!P || !g || !u || !r) return MLBA_EINVAL;
-    return note_work(P, do_blur(P, u, g, r, false, nullptr, s), s);
+    return note_work(P, do_blur(P, u, g, r, false, nullptr, true, s), s);
 }
 
 int mlba_apply_At(mlba_plan_t P, const float* y, float* w, hipStream_t s) {
@@ -1286,14 +1304,15 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
     // and for MLBA with the blur evaluated by FFTs, the residual is formed in
     // the spectrum (F g computed once here) and an iteration is the synthesis
     // and one 2-D transform pair
-    const bool fold4 = (alg4 || (!alg2 && P->blur_fft)) && P->bc == MLBA_BC_PERIODIC &&
+    const bool taps = !implicit && !alg4 && !alg2;  // the explicit state's blurs keep the order of the taps
+    const bool fold4 = (alg4 || (!alg2 && uses_fft(P, taps))) && P->bc == MLBA_BC_PERIODIC &&
                        P->precond == MLBA_PRECOND_BCCB && P->ghat && (P->n / 2 + 1) <= P->partials_cap;
-    const bool fused = !fold4 && !alg4 && !alg2 && fused_fft_path(P);
+    const bool fused = !fold4 && !alg4 && !alg2 && fused_fft_path(P, taps);
     if (fold4 && iters > 0) {
         HIPCHK(launch_fft_rows_r2c(g, P->n, (float2*)P->swork, P->ts, P->fd, P->tw, s));
         HIPCHK(launch_fft_cols_complex((const float2*)P->swork, P->n, P->ts, P->ghat, P->fd, P->tw, s));
     }
-    const bool fused_ar = !ns && !alg2 && fused_ar_path(P);  // MLBA or Algorithm 4
+    const bool fused_ar = !ns && !alg2 && fused_ar_path(P, taps);  // MLBA or Algorithm 4
     for (int i = 0; i < iters; ++i) {
         if (i - ring_base >= P->rn_cap) {
             if (track) STCHK(drain(i));
@@ -1377,7 +1396,7 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
             if (implicit) {
                 STCHK(do_blurT_acc(P, P->t, z, s));
             } else {
-                STCHK(do_blurT(P, P->t, P->w, s));
+                STCHK(do_blurT(P, P->t, P->w, s, taps));
                 STCHK(do_analysis(P, P->w, z, true, s));
             }
             P->prof_cur = -1;
@@ -1423,7 +1442,7 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
             HIPCHK(launch_fc_residual_precond_rows(P->fc, P->n, P->p, g, P->r, P->partials, &np, precond_rows(P), s));
             MARK(BLUR, FC_RESIDUAL_PRECOND_ROWS);
         } else {
-            STCHK(do_blur(P, P->u, g, P->r, true, &np, s));
+            STCHK(do_blur(P, P->u, g, P->r, true, &np, taps, s));
         }
         HIPCHK(launch_sum_partials(P->partials, np, P->rn + (i - ring_base), s));
         MARK(BLUR, REDUCE);
@@ -1468,7 +1487,7 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
         if (implicit) {
             STCHK(do_blurT_acc(P, P->t, z, s));
         } else {
-            STCHK(do_blurT(P, P->t, P->w, s));
+            STCHK(do_blurT(P, P->t, P->w, s, taps));
             STCHK(do_analysis(P, P->w, z, true, s));
         }
         P->prof_cur = -1;

@@ -30,10 +30,11 @@ struct mlba_plan_s {
     int n = 0, p = 0, c = 0, N = 0, bc = 0, precond = 0, levels = 0, bands = 0;
     mlba::FftDesc fd{};
     int ts = 0;                // row stride of the transposed spectral workspace
-    int conv_rows[2] = {0, 0}; // output rows per thread of the A / A^T blur (0: by occupancy)
-    int blur_fft = 0;          // rectangular model: A and A^T by FFTs of an M x M grid
+    int blur_fft = 0;          // A and A^T by FFTs of an M x M grid
+    int blur_fft_taps = 0;     // the same choice where the direct blur keeps the order of the taps
     mlba::FftConv fc{};        // its plan and buffers (allocated on first use)
     float* psf = nullptr;
+    uint4* taps[2] = {nullptr, nullptr};  // split taps of the direct A^T and A
     float* spec = nullptr;     // BCCB: [n/2+1][n] |Lambda|^2 (transposed); DCT, AR: [n][n] lambda^2
     float2* lamc = nullptr;    // square models, BCCB: Lambda_c of the centred PSF (layout of spec)
     float2* ghat = nullptr;    // periodic model, BCCB: F g of the current restoration (layout of spec)
@@ -115,6 +116,8 @@ inline mlba::BatchImage plan_desc(const mlba_plan_s* P) {
     d.z = P->z;
     d.zin = P->z;
     d.psf = P->psf;
+    d.taps[0] = P->taps[0];
+    d.taps[1] = P->taps[1];
     d.spec = P->spec;
     d.swork = P->swork;
     d.tw = P->tw;

@@ -63,7 +63,7 @@ struct mlba_unrolled_s {
     std::vector<ImgBufs> bufs;
     std::vector<void*> allocs;
     int* maps = nullptr;
-    Map conv_a, conv_at, pre[3], syn[5], ana[5], adj[5], corr, fill;
+    Map tap_a, tap_at, conv_a, conv_at, pre[3], syn[5], ana[5], adj[5], corr, fill;
     double* dblock = nullptr;  // running partials (doubles), zeroed per backward
     size_t dcount = 0;
     float* eblock = nullptr;   // eacc of every image, zeroed per backward
@@ -133,17 +133,20 @@ size_t spec_elems(const BatchImage& b) { return (size_t)(b.n / 2 + 1) * b.n; }
 // segment j covers iterations [j*ce, j*ce + seg_len(j))
 int seg_len(const mlba_unrolled_s* U, int j) { return std::min(U->ce, U->iters - j * U->ce); }
 
-// One forward iteration with descriptor table T.
+// One forward iteration with descriptor table T.  Its blurs keep the order of
+// the taps (tapconv.hip); the reverse sweep, which is linear between the active
+// sets, runs them on the matrix cores.
 int enqueue_step(const mlba_unrolled_s* U, const BatchImage* T, hipStream_t s) {
     for (int lev = U->levels; lev >= 1; --lev) {
         const Map& m = U->syn[lev];
         HIPCHK(launch_synthesis_batched(T, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 0, s));
     }
-    HIPCHK(launch_conv_batched(T, U->conv_a.bmap, U->conv_a.bfirst, U->conv_a.nblocks, 1, U->p, nullptr, s));
+    HIPCHK(launch_tapconv_batched(T, U->tap_a.bmap, U->tap_a.bfirst, U->tap_a.nblocks, 1, U->p, 1, nullptr, s));
     for (int pass = 0; pass < 3; ++pass)
         HIPCHK(launch_precond_batched(T, U->pre[pass].bmap, U->pre[pass].bfirst, U->pre[pass].nblocks, pass,
                                       MLBA_PRECOND_BCCB, U->nmax, s, U->any_len));
-    HIPCHK(launch_conv_batched(T, U->conv_at.bmap, U->conv_at.bfirst, U->conv_at.nblocks, 0, U->p, nullptr, s));
+    HIPCHK(launch_tapconv_batched(T, U->tap_at.bmap, U->tap_at.bfirst, U->tap_at.nblocks, 0, U->p, 1,
+                                  nullptr, s));
     for (int lev = 1; lev <= U->levels; ++lev) {
         const Map& m = U->ana[lev];
         HIPCHK(launch_analysis_batched(T, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), s));
@@ -257,9 +260,13 @@ int mlba_unrolled_create(mlba_unrolled_t* out, int count, const mlba_plan_t* pla
         build_map(t, hm, offs, m);
         order.push_back(&m);
     };
-    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(U->base[i], 1);
+    for (int i = 0; i < count; ++i) t[i] = tapconv_batched_tiles(U->base[i], 1);
+    add(U->tap_a);
+    for (int i = 0; i < count; ++i) t[i] = tapconv_batched_tiles(U->base[i], 0);
+    add(U->tap_at);
+    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(U->base[i], 1, U->p);
     add(U->conv_a);
-    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(U->base[i], 0);
+    for (int i = 0; i < count; ++i) t[i] = conv_batched_tiles(U->base[i], 0, U->p);
     add(U->conv_at);
     for (int pass = 0; pass < 3; ++pass) {
         for (int i = 0; i < count; ++i) t[i] = precond_pass_tiles(U->base[i], pass);
