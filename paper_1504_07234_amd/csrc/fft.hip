@@ -21,6 +21,7 @@
 #include "artrans.hpp"
 #include "common.hpp"
 #include "fft_core.hpp"
+#include "fft_seq.hpp"
 #include "kernels.hpp"
 
 namespace mlba {
@@ -604,6 +605,15 @@ __global__ __launch_bounds__(kBlock) void fft_cols_residual_kernel(float2* __res
 // to the rows it reads and transforms the new res; the inverse row pass
 // writes z = P res with the partial sums of res . z per workgroup.  The
 // arithmetic of every value is that of the separate update and dot kernels.
+// the update of Algorithm 2's vectors at flat index i
+__device__ __forceinline__ float pcg_row_value(const PcgVec& v, bool on, float a, size_t i) {
+    if (!on) return v.res[i];
+    v.t[i] = fmaf(a, v.d[i], v.t[i]);
+    const float r = fmaf(-a, v.q[i], v.res[i]);
+    v.res[i] = r;
+    return r;
+}
+
 template <int NT>
 __global__ __launch_bounds__(kBlock) void pcg_rows_r2c_kernel(int n, float2* __restrict__ T, int ts, FftDesc fd,
                                                               const float2* __restrict__ tw, int G, int seq_shift,
@@ -612,13 +622,7 @@ __global__ __launch_bounds__(kBlock) void pcg_rows_r2c_kernel(int n, float2* __r
     const bool on = *v.act != 0.0;
     const float a = on ? (float)(*v.rho / *v.pq) : 0.0f;
     fft_rows_r2c_body_f<NT>(
-        [&](size_t i) {
-            if (!on) return v.res[i];
-            v.t[i] = fmaf(a, v.d[i], v.t[i]);
-            const float r = fmaf(-a, v.q[i], v.res[i]);
-            v.res[i] = r;
-            return r;
-        },
+        [&](size_t i) { return pcg_row_value(v, on, a, i); },
         n, T, ts, fd, tw, G, seq_shift, xcd_block(blockIdx.x, gridDim.x), buf);
 }
 
@@ -714,6 +718,119 @@ __global__ __launch_bounds__(kBlock) void dct_rows_inv_kernel(const float* __res
                                                               int accum) {
     extern __shared__ float2 buf[];
     dct_rows_inv_body<NT>(Tr, n, ts, dst, fd, tw, dtw, G, seq_shift, xcd_block(blockIdx.x, gridDim.x), buf, accum);
+}
+
+// ---- single-image kernels of the compiled short lengths (fft_seq.hpp) --------
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void fft_rows_r2c_seq_kernel(const float* __restrict__ src,
+                                                                        float2* __restrict__ T, int ts,
+                                                                        const float2* __restrict__ tw) {
+    extern __shared__ float2 buf[];
+    seq_rows_r2c<N, seq_block(N)>([&](size_t i) { return src[i]; }, T, ts, tw, xcd_block(blockIdx.x, gridDim.x), buf);
+}
+
+// red_out: as in fft_cols_kernel
+template <int N>
+__device__ __forceinline__ void seq_reduce(const double* __restrict__ red_in, int red_count,
+                                           double* __restrict__ red_out) {
+    constexpr int THREADS = seq_block(N);
+    if (!red_out || blockIdx.x != 0) return;
+    __shared__ double red[kBlock / 64];
+    double acc = 0.0;
+    for (int i0 = threadIdx.x; i0 < red_count; i0 += 4 * THREADS) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = i0 + u * THREADS < red_count ? red_in[i0 + u * THREADS] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += v[u];
+    }
+    const double t = block_sum(acc, red);
+    if (threadIdx.x == 0) *red_out = t;
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void fft_cols_seq_kernel(float2* __restrict__ T, int ts,
+                                                                    const float* __restrict__ spec, float alpha,
+                                                                    float inv, const float2* __restrict__ tw,
+                                                                    const float2* __restrict__ lamc,
+                                                                    const double* __restrict__ red_in, int red_count,
+                                                                    double* __restrict__ red_out) {
+    extern __shared__ float2 buf[];
+    seq_reduce<N>(red_in, red_count, red_out);
+    seq_cols<N, seq_block(N)>(T, ts, spec, alpha, inv, tw, blockIdx.x, buf, lamc);
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void fft_rows_c2r_seq_kernel(const float2* __restrict__ T, int ts,
+                                                                        float* __restrict__ dst,
+                                                                        const float2* __restrict__ tw, int accum) {
+    extern __shared__ float2 buf[];
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    if (accum) seq_rows_c2r<N, seq_block(N)>(T, ts, [&](size_t i, float v) { dst[i] += v; }, tw, blk, buf);
+    else seq_rows_c2r<N, seq_block(N)>(T, ts, [&](size_t i, float v) { dst[i] = v; }, tw, blk, buf);
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void pcg_rows_r2c_seq_kernel(float2* __restrict__ T, int ts,
+                                                                        const float2* __restrict__ tw, PcgVec v) {
+    extern __shared__ float2 buf[];
+    const bool on = *v.act != 0.0;
+    const float a = on ? (float)(*v.rho / *v.pq) : 0.0f;
+    seq_rows_r2c<N, seq_block(N)>([&](size_t i) { return pcg_row_value(v, on, a, i); }, T, ts, tw,
+                                  xcd_block(blockIdx.x, gridDim.x), buf);
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void pcg_rows_c2r_seq_kernel(const float2* __restrict__ T, int ts,
+                                                                        float* __restrict__ z,
+                                                                        const float* __restrict__ res,
+                                                                        const float2* __restrict__ tw,
+                                                                        double* __restrict__ part) {
+    extern __shared__ float2 buf[];
+    __shared__ double red[kBlock / 64];
+    double acc = 0.0;
+    seq_rows_c2r<N, seq_block(N)>(
+        T, ts,
+        [&](size_t i, float val) {
+            z[i] = val;
+            acc += (double)res[i] * (double)val;
+        },
+        tw, xcd_block(blockIdx.x, gridDim.x), buf);
+    static_assert((N / 2) % seq_group(N, seq_block(N)) == 0, "every sequence is live: the whole workgroup gets here");
+    const double t = block_sum(acc, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void dct_rows_fwd_seq_kernel(const float* __restrict__ src,
+                                                                        float* __restrict__ Tr, int ts,
+                                                                        const float2* __restrict__ tw,
+                                                                        const float2* __restrict__ dtw) {
+    extern __shared__ float2 buf[];
+    seq_dct_rows_fwd<N, seq_block(N)>(src, Tr, ts, tw, dtw, xcd_block(blockIdx.x, gridDim.x), buf);
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void dct_cols_seq_kernel(float* __restrict__ Tr, int ts,
+                                                                    const float* __restrict__ spec, float alpha,
+                                                                    float inv, const float2* __restrict__ tw,
+                                                                    const float2* __restrict__ dtw,
+                                                                    const float* __restrict__ lamr,
+                                                                    const double* __restrict__ red_in, int red_count,
+                                                                    double* __restrict__ red_out) {
+    extern __shared__ float2 buf[];
+    seq_reduce<N>(red_in, red_count, red_out);
+    seq_dct_cols<N, seq_block(N)>(Tr, ts, spec, alpha, inv, tw, dtw, blockIdx.x, buf, lamr);
+}
+
+template <int N>
+__global__ __launch_bounds__(seq_block(N)) void dct_rows_inv_seq_kernel(const float* __restrict__ Tr, int ts,
+                                                                        float* __restrict__ dst,
+                                                                        const float2* __restrict__ tw,
+                                                                        const float2* __restrict__ dtw, int accum) {
+    extern __shared__ float2 buf[];
+    seq_dct_rows_inv<N, seq_block(N)>(Tr, ts, dst, tw, dtw, xcd_block(blockIdx.x, gridDim.x), buf, accum);
 }
 
 // Cosine spectra of the symmetrised PSF H~ (reflective blur, Algorithm 3;
@@ -1094,9 +1211,32 @@ int precond_pass_tiles(const BatchImage& I, int pass) {
     if (I.precond == 2) return 0;  // P = I: the descriptor aliases t to r
     if (I.precond == 3) return pass == 3 ? 0 : (I.n + 1) / 2;  // antireflective: one row pair per workgroup
     if (pass == 3) pass = 1;
+    if (seq_length(I.n)) {
+        const int g = seq_group(I.n, kBlock), seqs = pass == 1 && I.precond == 0 ? I.n / 2 + 1 : I.n / 2;
+        return (seqs + g - 1) / g;
+    }
     if (pass != 1) return I.n / (2 * I.fft_rows_g);
     if (I.precond == 0) return (I.n / 2 + 1 + I.fft_cols_c - 1) / I.fft_cols_c;
     return (I.n / 2 + I.fft_cols_c - 1) / I.fft_cols_c;
+}
+
+// the pass of an image of a compiled short length
+template <int PASS, int PRECOND, int N>
+__device__ __forceinline__ void precond_seq_pass(const BatchImage& I, float inv, int blk, float2* buf) {
+    float2* T = (float2*)I.swork;
+    float* Tr = (float*)I.swork;
+    if constexpr (PRECOND == 0) {
+        if (PASS == 0)
+            seq_rows_r2c<N, kBlock>([r = I.r](size_t i) { return r[i]; }, T, I.ts, I.tw, blk, buf);
+        if (PASS == 1)
+            seq_cols<N, kBlock>(T, I.ts, I.spec, I.alpha, inv, I.tw, blk, buf, nullptr, I.sstore, I.sfwd, I.eacc);
+        if (PASS == 2) seq_rows_c2r<N, kBlock>(T, I.ts, [t = I.t](size_t i, float v) { t[i] = v; }, I.tw, blk, buf);
+        if (PASS == 3) seq_cols_inverse_real<N, kBlock>(I.eacc, T, I.ts, I.tw, blk, buf);
+    } else {
+        if (PASS == 0) seq_dct_rows_fwd<N, kBlock>(I.r, Tr, I.ts, I.tw, I.dtw, blk, buf);
+        if (PASS == 1) seq_dct_cols<N, kBlock>(Tr, I.ts, I.spec, I.alpha, inv, I.tw, I.dtw, blk, buf);
+        if (PASS == 2) seq_dct_rows_inv<N, kBlock>(Tr, I.ts, I.t, I.tw, I.dtw, blk, buf);
+    }
 }
 
 template <int PASS, int PRECOND, int NB>
@@ -1122,6 +1262,17 @@ __global__ __launch_bounds__(kBlock) void precond_batched_kernel(const BatchImag
         if (PASS == 2) ar_rows_inv_body<NB>(Tr, n, I.ts, I.t, I.fd, I.tw, 1, I.fft_rows_shift, blk, buf, 0);
         return;
     }
+    if constexpr (PRECOND != 3) {
+        switch (n) {
+#define MLBA_SEQ_PASS(N)                                          \
+    case N:                                                       \
+        precond_seq_pass<PASS, PRECOND, N>(I, inv, blk, buf);     \
+        return;
+            MLBA_SEQ_LENGTHS(MLBA_SEQ_PASS)
+#undef MLBA_SEQ_PASS
+            default: break;
+        }
+    }
     if (PRECOND == 0) {
         float2* T = (float2*)I.swork;
         if (PASS == 0) fft_rows_r2c_body<NB>(I.r, n, T, I.ts, I.fd, I.tw, I.fft_rows_g, I.fft_rows_shift, blk, buf);
@@ -1146,7 +1297,11 @@ __global__ __launch_bounds__(kBlock) void precond_batched_kernel(const BatchImag
 hipError_t launch_precond_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int pass,
                                   int precond, int nmax, hipStream_t s, int any_len) {
     if (nblocks <= 0) return hipSuccess;
-    const size_t lds = lds_bytes(FFT_MAX_ELEMS, nmax);
+    size_t lds = lds_bytes(FFT_MAX_ELEMS, nmax);
+#define MLBA_SEQ_LDS(N) \
+    if (N <= nmax && seq_lds_bytes(N, seq_group(N, kBlock)) > lds) lds = seq_lds_bytes(N, seq_group(N, kBlock));
+    MLBA_SEQ_LENGTHS(MLBA_SEQ_LDS)
+#undef MLBA_SEQ_LDS
 #define MLBA_PB(PA, PC)                                                                                            \
     do {                                                                                                           \
         if (any_len)                                                                                               \
@@ -1176,8 +1331,30 @@ hipError_t launch_precond_batched(const BatchImage* imgs, const int* bmap, const
     return hipGetLastError();
 }
 
+// Launches KERNEL<n> over `count` sequences and returns, for the compiled short lengths.
+#define MLBA_SEQ_LAUNCH_CASE(N, KERNEL, COUNT, ...)                                                              \
+    case N:                                                                                                      \
+        hipLaunchKernelGGL(KERNEL<N>, dim3(((COUNT) + seq_group(N, seq_block(N)) - 1) / seq_group(N, seq_block(N))), \
+                           dim3(seq_block(N)), seq_lds_bytes(N, seq_group(N, seq_block(N))), s, __VA_ARGS__);    \
+        return hipGetLastError();
+#define MLBA_SEQ_LAUNCH(n, KERNEL, COUNT, ...)                  \
+    switch (n) {                                                \
+        MLBA_SEQ_LAUNCH_CASE(64, KERNEL, COUNT, __VA_ARGS__)    \
+        MLBA_SEQ_LAUNCH_CASE(96, KERNEL, COUNT, __VA_ARGS__)    \
+        MLBA_SEQ_LAUNCH_CASE(128, KERNEL, COUNT, __VA_ARGS__)   \
+        MLBA_SEQ_LAUNCH_CASE(192, KERNEL, COUNT, __VA_ARGS__)   \
+        MLBA_SEQ_LAUNCH_CASE(256, KERNEL, COUNT, __VA_ARGS__)   \
+        MLBA_SEQ_LAUNCH_CASE(384, KERNEL, COUNT, __VA_ARGS__)   \
+        MLBA_SEQ_LAUNCH_CASE(512, KERNEL, COUNT, __VA_ARGS__)   \
+        MLBA_SEQ_LAUNCH_CASE(768, KERNEL, COUNT, __VA_ARGS__)   \
+        MLBA_SEQ_LAUNCH_CASE(1024, KERNEL, COUNT, __VA_ARGS__)  \
+        MLBA_SEQ_LAUNCH_CASE(1536, KERNEL, COUNT, __VA_ARGS__)  \
+        default: break;                                         \
+    }
+
 hipError_t launch_fft_rows_r2c(const float* src, int n, float2* T, int ts, const FftDesc& fd, const float2* tw,
                                hipStream_t s) {
+    MLBA_SEQ_LAUNCH(n, fft_rows_r2c_seq_kernel, n / 2, src, T, ts, tw)
     const int G = pick_pairs_per_block(n);
     const size_t lds = lds_bytes(fft_lds_elems(G * n, n), n);
     if (n == kFixedN && G == 1)
@@ -1198,6 +1375,8 @@ static hipError_t launch_cols(float2* T, int n, int ts, const float* spec, float
                               double* red_out = nullptr) {
     const int CC = pick_cols_per_block(n);
     const int half = n / 2 + 1;
+    if (mode == 0 && !alpha_dev)
+        MLBA_SEQ_LAUNCH(n, fft_cols_seq_kernel, half, T, ts, spec, alpha, inv, tw, lamc, red_in, red_count, red_out)
     const size_t lds = lds_bytes(fft_lds_elems(CC * n, n), n);
     if (n == kFixedN && CC == 1)
         hipLaunchKernelGGL(fft_cols_kernel<kFixedN>, dim3(half), dim3(kBlock), lds, s, T, n, ts, spec, alpha, inv, fd,
@@ -1266,6 +1445,7 @@ hipError_t launch_fft_cols_power(const float2* T, int n, int ts, float* spec, co
 
 hipError_t launch_fft_rows_c2r(const float2* T, int n, int ts, float* dst, const FftDesc& fd, const float2* tw,
                                hipStream_t s, int accum) {
+    MLBA_SEQ_LAUNCH(n, fft_rows_c2r_seq_kernel, n / 2, T, ts, dst, tw, accum)
     const int G = pick_pairs_per_block(n);
     const size_t lds = lds_bytes(fft_lds_elems(G * n, n), n);
     if (n == kFixedN && G == 1)
@@ -1282,6 +1462,7 @@ hipError_t launch_fft_rows_c2r(const float2* T, int n, int ts, float* dst, const
 
 hipError_t launch_pcg_rows_r2c(int n, float2* T, int ts, const FftDesc& fd, const float2* tw, const PcgVec& v,
                                hipStream_t s) {
+    MLBA_SEQ_LAUNCH(n, pcg_rows_r2c_seq_kernel, n / 2, T, ts, tw, v)
     const int G = pick_pairs_per_block(n);
     const size_t lds = lds_bytes(fft_lds_elems(G * n, n), n);
     if (n == kFixedN && G == 1)
@@ -1296,13 +1477,16 @@ hipError_t launch_pcg_rows_r2c(int n, float2* T, int ts, const FftDesc& fd, cons
     return hipGetLastError();
 }
 
-int pcg_rows_c2r_partials(int n) { return n / (2 * pick_pairs_per_block(n)); }
+int pcg_rows_c2r_partials(int n) {
+    return seq_length(n) ? n / 2 / seq_group(n, seq_block(n)) : n / (2 * pick_pairs_per_block(n));
+}
 
 hipError_t launch_pcg_rows_c2r(const float2* T, int n, int ts, float* z, const float* res, const FftDesc& fd,
                                const float2* tw, double* part, int* n_part, hipStream_t s) {
+    *n_part = pcg_rows_c2r_partials(n);
+    MLBA_SEQ_LAUNCH(n, pcg_rows_c2r_seq_kernel, n / 2, T, ts, z, res, tw, part)
     const int G = pick_pairs_per_block(n);
     const size_t lds = lds_bytes(fft_lds_elems(G * n, n), n);
-    *n_part = n / (2 * G);
     if (n == kFixedN && G == 1)
         hipLaunchKernelGGL(pcg_rows_c2r_kernel<kFixedN>, dim3(n / 2), dim3(kBlock), lds, s, T, n, ts, z, res, fd, tw, 1,
                            seq_shift_for(1), part);
@@ -1317,6 +1501,7 @@ hipError_t launch_pcg_rows_c2r(const float2* T, int n, int ts, float* z, const f
 
 hipError_t launch_dct_rows_fwd(const float* src, int n, float* Tr, int ts, const FftDesc& fd, const float2* tw,
                                const float2* dtw, hipStream_t s) {
+    MLBA_SEQ_LAUNCH(n, dct_rows_fwd_seq_kernel, n / 2, src, Tr, ts, tw, dtw)
     const int G = pick_pairs_per_block(n);
     const size_t lds = lds_bytes(fft_lds_elems(G * n, n), n);
     if (n == kFixedN && G == 1)
@@ -1333,7 +1518,15 @@ hipError_t launch_dct_rows_fwd(const float* src, int n, float* Tr, int ts, const
 
 static hipError_t launch_dct_cols(float* Tr, int n, int ts, const float* spec, float alpha, float inv,
                                   const FftDesc& fd, const float2* tw, const float2* dtw, hipStream_t s,
-                                  const float* lamr, int mode, const double* alpha_dev) {
+                                  const float* lamr, int mode, const double* alpha_dev, const double* red_in = nullptr,
+                                  int red_count = 0, double* red_out = nullptr) {
+    if (mode == 0)
+        MLBA_SEQ_LAUNCH(n, dct_cols_seq_kernel, n / 2, Tr, ts, spec, alpha, inv, tw, dtw, lamr, red_in, red_count,
+                        red_out)
+    if (red_out) {  // no reduction in the run-time kernels
+        const hipError_t e = launch_sum_partials(red_in, red_count, red_out, s);
+        if (e != hipSuccess) return e;
+    }
     int CP = pick_cols_per_block(n);
     const int pairs = n / 2;
     const size_t lds = lds_bytes(fft_lds_elems(CP * n, n), n);
@@ -1351,8 +1544,8 @@ static hipError_t launch_dct_cols(float* Tr, int n, int ts, const float* spec, f
 
 hipError_t launch_dct_cols_filter(float* Tr, int n, int ts, const float* spec, float alpha, float inv,
                                   const FftDesc& fd, const float2* tw, const float2* dtw, hipStream_t s,
-                                  const float* lamr) {
-    return launch_dct_cols(Tr, n, ts, spec, alpha, inv, fd, tw, dtw, s, lamr, 0, nullptr);
+                                  const float* lamr, const double* red_in, int red_count, double* red_out) {
+    return launch_dct_cols(Tr, n, ts, spec, alpha, inv, fd, tw, dtw, s, lamr, 0, nullptr, red_in, red_count, red_out);
 }
 
 hipError_t launch_dct_cols_forward(float* Tr, int n, int ts, const FftDesc& fd, const float2* tw, const float2* dtw,
@@ -1368,6 +1561,7 @@ hipError_t launch_dct_cols_filter_inverse(float* Tr, int n, int ts, const float*
 
 hipError_t launch_dct_rows_inv(const float* Tr, int n, int ts, float* dst, const FftDesc& fd, const float2* tw,
                                const float2* dtw, hipStream_t s, int accum) {
+    MLBA_SEQ_LAUNCH(n, dct_rows_inv_seq_kernel, n / 2, Tr, ts, dst, tw, dtw, accum)
     const int G = pick_pairs_per_block(n);
     const size_t lds = lds_bytes(fft_lds_elems(G * n, n), n);
     if (n == kFixedN && G == 1)

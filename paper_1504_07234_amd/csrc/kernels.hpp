@@ -391,7 +391,9 @@ hipError_t launch_dct_rows_fwd(const float* src, int n, float* Tr, int ts, const
                                const float2* tw, const float2* dtw, hipStream_t s);
 hipError_t launch_dct_cols_filter(float* Tr, int n, int ts, const float* spec, float alpha, float inv,
                                   const FftDesc& fd, const float2* tw, const float2* dtw,
-                                  hipStream_t s, const float* lamr = nullptr);  // lamr: times lambda (Alg. 4)
+                                  hipStream_t s, const float* lamr = nullptr,  // lamr: times lambda (Alg. 4)
+                                  const double* red_in = nullptr, int red_count = 0,
+                                  double* red_out = nullptr);  // red_*: as in launch_fft_cols_filter
 hipError_t launch_dct_rows_inv(const float* Tr, int n, int ts, float* dst, const FftDesc& fd,
                                const float2* tw, const float2* dtw, hipStream_t s, int accum = 0);
 // columns: DCT-II only (Tr then holds the 2-D coefficients), and the filter

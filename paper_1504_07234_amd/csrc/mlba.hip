@@ -329,14 +329,23 @@ int do_blurT(mlba_plan_s* P, const float* y, float* w, hipStream_t s, bool taps 
     return MLBA_OK;
 }
 
-int do_precond(mlba_plan_s* P, const float* r, float* t, double alpha, hipStream_t s) {
+// t = P r.  red (optional): partials of ||r||^2 that P's column pass, or a
+// launch of its own where it cannot, sums into *red.out.
+struct NormSum {
+    const double* part = nullptr;
+    int count = 0;
+    double* out = nullptr;
+};
+
+int do_precond(mlba_plan_s* P, const float* r, float* t, double alpha, hipStream_t s, NormSum red = {}) {
     const int n = P->n;
     const float inv = (float)(1.0 / ((double)n * (double)n));
     if (P->precond == MLBA_PRECOND_BCCB) {
         float2* T = (float2*)P->swork;
         HIPCHK(launch_fft_rows_r2c(r, n, T, P->ts, P->fd, P->tw, s));
         MARK(PRECOND, FFT_ROWS_FWD);
-        HIPCHK(launch_fft_cols_filter(T, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, s));
+        HIPCHK(launch_fft_cols_filter(T, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, s, nullptr, red.part,
+                                      red.count, red.out));
         MARK(PRECOND, FFT_COLS);
         HIPCHK(launch_fft_rows_c2r(T, n, P->ts, t, P->fd, P->tw, s));
         MARK(PRECOND, FFT_ROWS_INV);
@@ -344,7 +353,8 @@ int do_precond(mlba_plan_s* P, const float* r, float* t, double alpha, hipStream
         float* Tr = (float*)P->swork;
         HIPCHK(launch_dct_rows_fwd(r, n, Tr, P->ts, P->fd, P->tw, P->dtw, s));
         MARK(PRECOND, FFT_ROWS_FWD);
-        HIPCHK(launch_dct_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, P->dtw, s));
+        HIPCHK(launch_dct_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, P->dtw, s, nullptr,
+                                      red.part, red.count, red.out));
         MARK(PRECOND, FFT_COLS);
         HIPCHK(launch_dct_rows_inv(Tr, n, P->ts, t, P->fd, P->tw, P->dtw, s));
         MARK(PRECOND, FFT_ROWS_INV);
@@ -352,11 +362,14 @@ int do_precond(mlba_plan_s* P, const float* r, float* t, double alpha, hipStream
         float* Tr = (float*)P->swork;
         HIPCHK(launch_ar_rows_fwd(r, n, Tr, P->ts, P->fd, P->tw, s));
         MARK(PRECOND, FFT_ROWS_FWD);
-        HIPCHK(launch_ar_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, nullptr, P->fd, P->tw, s));
+        HIPCHK(launch_ar_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, nullptr, P->fd, P->tw, s, red.part, red.count,
+                                     red.out));
         MARK(PRECOND, FFT_COLS);
         HIPCHK(launch_ar_rows_inv(Tr, n, P->ts, t, P->fd, P->tw, s));
         MARK(PRECOND, FFT_ROWS_INV);
-    } else if (r != t) {
+    } else {
+        if (red.out) HIPCHK(launch_sum_partials(red.part, red.count, red.out, s));
+        if (r == t) return MLBA_OK;
         HIPCHK(hipMemcpyAsync(t, r, (size_t)n * n * sizeof(float), hipMemcpyDeviceToDevice, s));
         MARK(PRECOND, OTHER);
     }
@@ -383,14 +396,16 @@ int compute_spectrum(mlba_plan_s* P, hipStream_t s) {
 }
 
 // t = C^T (C C^T + alpha I)^{-1} r (Algorithm 4), or accumulated into t (accum)
-int do_ct_precond(mlba_plan_s* P, const float* r, float* t, double alpha, int accum, hipStream_t s) {
+int do_ct_precond(mlba_plan_s* P, const float* r, float* t, double alpha, int accum, hipStream_t s,
+                  NormSum red = {}) {
     const int n = P->n;
     const float inv = (float)(1.0 / ((double)n * (double)n));
     if (P->precond == MLBA_PRECOND_BCCB) {
         float2* T = (float2*)P->swork;
         HIPCHK(launch_fft_rows_r2c(r, n, T, P->ts, P->fd, P->tw, s));
         MARK(PRECOND, FFT_ROWS_FWD);
-        HIPCHK(launch_fft_cols_filter(T, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, s, P->lamc));
+        HIPCHK(launch_fft_cols_filter(T, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, s, P->lamc, red.part,
+                                      red.count, red.out));
         MARK(PRECOND, FFT_COLS);
         HIPCHK(launch_fft_rows_c2r(T, n, P->ts, t, P->fd, P->tw, s, accum));
         MARK(PRECOND, FFT_ROWS_INV);
@@ -398,7 +413,8 @@ int do_ct_precond(mlba_plan_s* P, const float* r, float* t, double alpha, int ac
         float* Tr = (float*)P->swork;
         HIPCHK(launch_ar_rows_fwd(r, n, Tr, P->ts, P->fd, P->tw, s));
         MARK(PRECOND, FFT_ROWS_FWD);
-        HIPCHK(launch_ar_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, P->lamr, P->fd, P->tw, s));
+        HIPCHK(launch_ar_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, P->lamr, P->fd, P->tw, s, red.part, red.count,
+                                     red.out));
         MARK(PRECOND, FFT_COLS);
         HIPCHK(launch_ar_rows_inv(Tr, n, P->ts, t, P->fd, P->tw, s, accum));
         MARK(PRECOND, FFT_ROWS_INV);
@@ -406,7 +422,8 @@ int do_ct_precond(mlba_plan_s* P, const float* r, float* t, double alpha, int ac
         float* Tr = (float*)P->swork;
         HIPCHK(launch_dct_rows_fwd(r, n, Tr, P->ts, P->fd, P->tw, P->dtw, s));
         MARK(PRECOND, FFT_ROWS_FWD);
-        HIPCHK(launch_dct_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, P->dtw, s, P->lamr));
+        HIPCHK(launch_dct_cols_filter(Tr, n, P->ts, P->spec, (float)alpha, inv, P->fd, P->tw, P->dtw, s, P->lamr,
+                                      red.part, red.count, red.out));
         MARK(PRECOND, FFT_COLS);
         HIPCHK(launch_dct_rows_inv(Tr, n, P->ts, t, P->fd, P->tw, P->dtw, s, accum));
         MARK(PRECOND, FFT_ROWS_INV);
@@ -1444,12 +1461,17 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
         } else {
             STCHK(do_blur(P, P->u, g, P->r, true, &np, taps, s));
         }
-        HIPCHK(launch_sum_partials(P->partials, np, P->rn + (i - ring_base), s));
-        MARK(BLUR, REDUCE);
-        STCHK(check_stop(&hit));
-        if (hit) {
-            stopped = true;
-            break;
+        // the norm: summed inside P's column pass unless something asks for it first
+        const NormSum red{P->partials, np, P->rn + (i - ring_base)};
+        const bool later = !stop && !ns && !alg2 && !uses_fft(P, taps);
+        if (!later) {
+            HIPCHK(launch_sum_partials(red.part, red.count, red.out, s));
+            MARK(BLUR, REDUCE);
+            STCHK(check_stop(&hit));
+            if (hit) {
+                stopped = true;
+                break;
+            }
         }
         if (alg4) {
             // eq. (Alg4): the direction C^T (C C^T + alpha I)^{-1} r, no A^T product
@@ -1459,7 +1481,7 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
                                        as.ns_rho, as.alpha0, i == 0 ? 1 : 0, P->ahist + (i - ring_base),
                                        implicit ? 1 : 0, s));
             } else {
-                STCHK(do_ct_precond(P, P->r, dst, alpha[i], implicit ? 1 : 0, s));
+                STCHK(do_ct_precond(P, P->r, dst, alpha[i], implicit ? 1 : 0, s, later ? red : NormSum{}));
             }
             if (!implicit) STCHK(do_analysis(P, P->t, z, true, s));
             P->prof_cur = -1;
@@ -1483,7 +1505,7 @@ int mlba_restore(mlba_plan_t P, const float* g, const mlba_params* prm, float* f
             done = i + 1;
             continue;
         }
-        STCHK(do_precond(P, P->r, P->t, alpha[i], s));
+        STCHK(do_precond(P, P->r, P->t, alpha[i], s, later ? red : NormSum{}));
         if (implicit) {
             STCHK(do_blurT_acc(P, P->t, z, s));
         } else {
