@@ -1223,8 +1223,8 @@ int precond_pass_tiles(const BatchImage& I, int pass) {
 // the pass of an image of a compiled short length
 template <int PASS, int PRECOND, int N>
 __device__ __forceinline__ void precond_seq_pass(const BatchImage& I, float inv, int blk, float2* buf) {
-    float2* T = (float2*)I.swork;
-    float* Tr = (float*)I.swork;
+    float2* T = (float2*)(void*)I.swork;
+    float* Tr = (float*)(void*)I.swork;
     if constexpr (PRECOND == 0) {
         if (PASS == 0)
             seq_rows_r2c<N, kBlock>([r = I.r](size_t i) { return r[i]; }, T, I.ts, I.tw, blk, buf);
@@ -1254,7 +1254,7 @@ __global__ __launch_bounds__(kBlock) void precond_batched_kernel(const BatchImag
     const float inv = (float)(1.0 / ((double)n * (double)n));
     if constexpr (PRECOND == 3) {  // antireflective transform, one row pair per workgroup
         __shared__ float2 lin[2 * kArMaxBatch];
-        float* Tr = (float*)I.swork;
+        float* Tr = (float*)(void*)I.swork;
         if (PASS == 0) ar_rows_fwd_body<NB>(I.r, n, Tr, I.ts, I.fd, I.tw, 1, I.fft_rows_shift, blk, buf);
         if (PASS == 1)
             ar_cols_filter_body<NB>(Tr, n, I.ts, I.spec, I.alpha, nullptr, I.fd, I.tw, 1, I.fft_cols_shift, blk, buf,
@@ -1274,7 +1274,7 @@ __global__ __launch_bounds__(kBlock) void precond_batched_kernel(const BatchImag
         }
     }
     if (PRECOND == 0) {
-        float2* T = (float2*)I.swork;
+        float2* T = (float2*)(void*)I.swork;
         if (PASS == 0) fft_rows_r2c_body<NB>(I.r, n, T, I.ts, I.fd, I.tw, I.fft_rows_g, I.fft_rows_shift, blk, buf);
         if (PASS == 1)
             fft_cols_body<NB>(T, n, I.ts, I.spec, I.alpha, inv, I.fd, I.tw, I.fft_cols_c, 0, nullptr, I.fft_cols_shift,
@@ -1283,7 +1283,7 @@ __global__ __launch_bounds__(kBlock) void precond_batched_kernel(const BatchImag
         if (PASS == 3)
             fft_cols_inverse_real_body<NB>(I.eacc, T, n, I.ts, I.fd, I.tw, I.fft_cols_c, I.fft_cols_shift, blk, buf);
     } else {
-        float* Tr = (float*)I.swork;
+        float* Tr = (float*)(void*)I.swork;
         if (PASS == 0)
             dct_rows_fwd_body<NB>(I.r, n, Tr, I.ts, I.fd, I.tw, I.dtw, I.fft_rows_g, I.fft_rows_shift, blk, buf);
         if (PASS == 1)

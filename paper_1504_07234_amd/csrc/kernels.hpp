@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace mlba {
@@ -59,6 +61,25 @@ struct ConvJob {
     int acc;
 };
 
+// A device pointer that kernels read from memory.  The compiler cannot tell
+// that a plain pointer read there is global and would access it with flat
+// instructions, which also count as LDS accesses and so make every wait for LDS
+// a wait for memory; this member's type says it.
+template <class T>
+struct GlobalPtr {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((address_space(1))) T* Raw;
+#else
+    typedef T* Raw;
+#endif
+    Raw p;
+    GlobalPtr() = default;
+    __host__ __device__ GlobalPtr(T* q) : p((Raw)q) {}
+    template <class U, class = std::enable_if_t<std::is_convertible<U*, T*>::value>>
+    __host__ __device__ GlobalPtr(const GlobalPtr<U>& q) : GlobalPtr((T*)(U*)q) {}
+    __host__ __device__ operator T*() const { return (T*)p; }
+};
+
 // Per-image descriptor of a batch (device memory): sizes, model, parameters
 // and the plan's buffers.  All images of a batch share the framelet depth.
 struct BatchImage {
@@ -67,41 +88,41 @@ struct BatchImage {
     int pbase;  // first residual-norm partial of this image
     float alpha, delta;
     float mu[33];
-    const float* g;
-    float* f;
-    float* z;          // state written by the analysis update
-    const float* zin;  // state read by the synthesis and by the update (z unless a step writes a new slot)
-    float* u;
-    float* r;
-    float* t;
-    float* w;
-    float* wext;
-    float* tmp0;
-    float* tmp1;
-    const float* psf;
-    const uint4* taps[2];  // split taps: [0] A^T, [1] A (launch_conv_taps)
-    const float* spec;
-    void* swork;
-    const float2* tw;
-    const float2* dtw;
-    double* rn;  // ||r^k||^2 per iteration
+    GlobalPtr<const float> g;
+    GlobalPtr<float> f;
+    GlobalPtr<float> z;          // state written by the analysis update
+    GlobalPtr<const float> zin;  // state read by the synthesis and by the update (z unless a step writes a new slot)
+    GlobalPtr<float> u;
+    GlobalPtr<float> r;
+    GlobalPtr<float> t;
+    GlobalPtr<float> w;
+    GlobalPtr<float> wext;
+    GlobalPtr<float> tmp0;
+    GlobalPtr<float> tmp1;
+    GlobalPtr<const float> psf;
+    GlobalPtr<const uint4> taps[2];  // split taps: [0] A^T, [1] A (launch_conv_taps)
+    GlobalPtr<const float> spec;
+    GlobalPtr<void> swork;
+    GlobalPtr<const float2> tw;
+    GlobalPtr<const float2> dtw;
+    GlobalPtr<double> rn;  // ||r^k||^2 per iteration
     // implicit state (z = W omega): z holds omega (state_planes = 1, else
     // bands); the A^T blur accumulates into w (= omega) when blur_acc; the
     // low-pass chain low_1 .. low_{levels-1}; the shrink-synthesis
     // coefficients of levels 1 .. levels
     int state_planes;
     int blur_acc;
-    float* lows[3];
+    GlobalPtr<float> lows[3];
     SsCoef ss[4];
     // reverse sweep of unrolled iterations (null elsewhere)
-    float2* sstore;      // the preconditioner's filtered spectrum is stored here ([n/2+1][n])
-    const float2* sfwd;  // filtered spectrum of the forward step being reversed
-    float* eacc;         // += Re(conj(filtered) * sfwd), dense [n/2+1][n]
-    const float* zk;     // forward state z_k: its active set masks the cotangent update
-    float* zbar;         // state cotangent [bands][N][N]
-    const float* tk;     // forward t_k = P r_k (n x n)
-    const float* uk;     // forward u_k = W^T(delta S_mu(z_k)) (N x N)
-    float* dg;           // gradient of the observation (n x n)
+    GlobalPtr<float2> sstore;      // the preconditioner's filtered spectrum is stored here ([n/2+1][n])
+    GlobalPtr<const float2> sfwd;  // filtered spectrum of the forward step being reversed
+    GlobalPtr<float> eacc;         // += Re(conj(filtered) * sfwd), dense [n/2+1][n]
+    GlobalPtr<const float> zk;     // forward state z_k: its active set masks the cotangent update
+    GlobalPtr<float> zbar;         // state cotangent [bands][N][N]
+    GlobalPtr<const float> tk;     // forward t_k = P r_k (n x n)
+    GlobalPtr<const float> uk;     // forward u_k = W^T(delta S_mu(z_k)) (N x N)
+    GlobalPtr<float> dg;           // gradient of the observation (n x n)
     FftDesc fd;
 };
 
