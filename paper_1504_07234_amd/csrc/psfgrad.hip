@@ -23,39 +23,43 @@
 
 namespace mlba {
 
-constexpr int PC_TY = 32;  // output rows per tile
-constexpr int PC_TX = 64;  // output columns per tile
-constexpr int PC_RB = 8;   // lags q per thread item
-constexpr int PC_XC = 8;   // columns per register segment
+constexpr int PC_TY = 32;       // rows of a tile of the observed grid
+constexpr int PC_TX = 64;       // columns
+constexpr int PC_TS = PC_TX + 4;  // LDS row stride of the t and rbar tiles: 16 rows on distinct banks
 
+typedef float corr_f32x4 __attribute__((ext_vector_type(4)));
+
+// Lags come in blocks of 16 x 16.
 struct CorrShape {
-    int p, nch, padl, wr, wc, lsw, items, yg;
+    int nb, padl, wr, wc;
 };
 
 __host__ __device__ inline CorrShape corr_shape(int p) {
     CorrShape c;
-    c.p = p;
-    c.nch = (p + PC_RB - 1) / PC_RB;
-    c.padl = c.nch * PC_RB - p;
+    c.nb = (p + 15) / 16;
+    c.padl = 16 * c.nb - p;          // window columns left of the image for the lags past p
     c.wr = PC_TY + p - 1;
-    c.wc = PC_TX + p - 1 + c.padl;
-    c.lsw = c.wc | 1;
-    c.items = p * c.nch;
-    c.yg = c.items >= kBlock ? 1 : kBlock / c.items;
+    c.wc = PC_TX + 16 * c.nb - 1;
     return c;
 }
 
 static size_t corr_lds_floats(int p) {
     const CorrShape c = corr_shape(p);
-    const size_t win = 2 * (size_t)c.wr * c.lsw + 2 * PC_TY * PC_TX;
-    const size_t red = (size_t)c.yg * p * p;
-    return win > red ? win : red;
+    return 2 * (size_t)c.wr * c.wc + 2 * PC_TY * PC_TS;
 }
 
 int psf_corr_tiles(const BatchImage& I) {
     return ((I.n + PC_TX - 1) / PC_TX) * ((I.n + PC_TY - 1) / PC_TY);
 }
 
+// The correlation sums over pixels, so it is a matrix product over them: row r
+// of the window and the tile's rows r - (p-1) + a give
+//   C[q][a] += sum_x W[r][x + p-1-q] t[r - (p-1) + a][x],
+// 16 lags q by 16 lags a and four pixels per v_mfma_f32_16x16x4_f32 (float32
+// products and sums).  With one block of lags (p <= 16) the four waves share
+// the window's rows and add up in LDS; otherwise each wave takes whole blocks.
+// The vector form of this kernel read 46 LDS values for 128 multiply-adds and
+// was bound by them (47 us a step at 16 x 256 x 256, p = 15).
 __global__ __launch_bounds__(kBlock) void psf_corr_batched_kernel(const BatchImage* __restrict__ imgs,
                                                                   const int* __restrict__ bmap,
                                                                   const int* __restrict__ bfirst, int first,
@@ -73,101 +77,104 @@ __global__ __launch_bounds__(kBlock) void psf_corr_batched_kernel(const BatchIma
     const int by = local / gx;
     const int oy0 = by * PC_TY, ox0 = (local - by * gx) * PC_TX;
 
-    float* Wl = smem;                    // W^T zbar window
-    float* Ul = Wl + cs.wr * cs.lsw;     // u_k window
-    float* Tl = Ul + cs.wr * cs.lsw;     // t_k tile
-    float* Rl = Tl + PC_TY * PC_TX;      // rbar tile
+    float* Wl = smem;                  // W^T zbar window
+    float* Ul = Wl + cs.wr * cs.wc;    // u_k window
+    float* Tl = Ul + cs.wr * cs.wc;    // t_k tile
+    float* Rl = Tl + PC_TY * PC_TS;    // -rbar tile
     const float* wbar = I.u;
     const float* uk = I.uk;
-    for (int idx = threadIdx.x; idx < cs.wr * cs.wc; idx += kBlock) {
-        const int ly = idx / cs.wc, lx = idx - ly * cs.wc;
-        const int y = oy0 + ly, x = ox0 + lx - cs.padl;
-        const bool in = y < N && x >= 0 && x < N;
-        const size_t o = (size_t)y * N + x;
-        Wl[ly * cs.lsw + lx] = in ? wbar[o] : 0.0f;
-        Ul[ly * cs.lsw + lx] = in ? uk[o] : 0.0f;
+    // the tile's loads, then the window's in rounds of WU rows: all of a round
+    // in flight together
+    constexpr int PER = PC_TY * PC_TX / kBlock, WU = 12;
+    float tv[PER], rv[PER], dv[PER];
+    const int ty = (int)threadIdx.x / PC_TX, tx = threadIdx.x % PC_TX;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int y = oy0 + ty + k * (kBlock / PC_TX), x = ox0 + tx;
+        const bool in = y < n && x < n;
+        const size_t o = in ? (size_t)y * n + x : 0;
+        const float a = I.tk[o], b = I.t[o], c = I.dg && !first ? I.dg[o] : 0.0f;
+        tv[k] = in ? a : 0.0f;
+        rv[k] = in ? b : 0.0f;
+        dv[k] = c;
+    }
+    {
+        const int lx = threadIdx.x & 127, x = ox0 + lx - cs.padl, ly0 = (int)threadIdx.x >> 7;
+        const bool col = lx < cs.wc && x >= 0 && x < N;
+        for (int l0 = ly0; l0 < cs.wr; l0 += WU * (kBlock / 128)) {
+            float w[WU], u[WU];
+#pragma unroll
+            for (int k = 0; k < WU; ++k) {
+                const int y = oy0 + l0 + k * (kBlock / 128);
+                const bool in = col && y < N;
+                const size_t o = in ? (size_t)y * N + x : 0;
+                w[k] = wbar[o];
+                u[k] = uk[o];
+                if (!in) w[k] = u[k] = 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < WU; ++k) {
+                const int ly = l0 + k * (kBlock / 128);
+                if (lx < cs.wc && ly < cs.wr) {
+                    Wl[ly * cs.wc + lx] = w[k];
+                    Ul[ly * cs.wc + lx] = u[k];
+                }
+            }
+        }
     }
     double dot = 0.0;
-    for (int idx = threadIdx.x; idx < PC_TY * PC_TX; idx += kBlock) {
-        const int ly = idx / PC_TX, lx = idx - ly * PC_TX;
-        const int y = oy0 + ly, x = ox0 + lx;
-        float tv = 0.0f, rv = 0.0f;
-        if (y < n && x < n) {
-            const size_t o = (size_t)y * n + x;
-            tv = I.tk[o];
-            rv = I.t[o];
-            if (I.dg) I.dg[o] = first ? rv : I.dg[o] + rv;
-            dot += (double)rv * (double)tv;
-        }
-        Tl[idx] = tv;
-        Rl[idx] = rv;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int ly = ty + k * (kBlock / PC_TX), y = oy0 + ly, x = ox0 + tx;
+        if (I.dg && y < n && x < n) I.dg[(size_t)y * n + x] = first ? rv[k] : dv[k] + rv[k];
+        dot += (double)rv[k] * (double)tv[k];
+        Tl[ly * PC_TS + tx] = tv[k];
+        Rl[ly * PC_TS + tx] = -rv[k];
     }
     __syncthreads();
 
-    // thread item (a, chunk) accumulates lags q = chunk*8 + i over rows yg, yg+YG, ...
-    float acc[PC_RB];
-    int a_it = -1, c_it = 0, yg_it = 0;
-    const int total = cs.items * cs.yg;
-    // more than one item per thread only when items >= kBlock (then yg == 1)
-    for (int it = threadIdx.x; it < total; it += kBlock) {
-        const int item = it % cs.items;
-        const int yg = it / cs.items;
-        const int a = item / cs.nch, ch = item - (item / cs.nch) * cs.nch;
-#pragma unroll
-        for (int i = 0; i < PC_RB; ++i) acc[i] = 0.0f;
-        for (int yl = yg; yl < PC_TY; yl += cs.yg) {
-            const float* wrow = Wl + (yl + p - 1 - a) * cs.lsw;
-            const float* urow = Ul + (yl + p - 1 - a) * cs.lsw;
-            const float* trow = Tl + yl * PC_TX;
-            const float* rrow = Rl + yl * PC_TX;
-            const int sbase = p - 1 - ch * PC_RB - (PC_RB - 1) + cs.padl;
-            for (int x0 = 0; x0 < PC_TX; x0 += PC_XC) {
-                float tv[PC_XC], rv[PC_XC], ws[PC_XC + PC_RB - 1], us[PC_XC + PC_RB - 1];
-#pragma unroll
-                for (int k = 0; k < PC_XC; ++k) {
-                    tv[k] = trow[x0 + k];
-                    rv[k] = rrow[x0 + k];
-                }
-#pragma unroll
-                for (int k = 0; k < PC_XC + PC_RB - 1; ++k) {
-                    ws[k] = wrow[sbase + x0 + k];
-                    us[k] = urow[sbase + x0 + k];
-                }
-#pragma unroll
-                for (int xi = 0; xi < PC_XC; ++xi)
-#pragma unroll
-                    for (int i = 0; i < PC_RB; ++i) {
-                        acc[i] = fmaf(tv[xi], ws[xi + PC_RB - 1 - i], acc[i]);
-                        acc[i] = fmaf(-rv[xi], us[xi + PC_RB - 1 - i], acc[i]);
-                    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, kk = lane >> 4;
+    const int split = cs.nb == 1 ? kBlock / 64 : 1;  // waves that share a block's window rows
+    for (int blk = split > 1 ? 0 : wave; blk < cs.nb * cs.nb; blk += kBlock / 64) {
+        const int bq = blk / cs.nb, ba = blk - bq * cs.nb;
+        corr_f32x4 c0 = {0.0f, 0.0f, 0.0f, 0.0f}, c1 = c0;
+        // lane's A column: lag q = 16 bq + m at pixel kk; its B row: lag a = 16 ba + m
+        const int acol = kk + p - 1 - (16 * bq + m) + cs.padl;
+        for (int r = split > 1 ? wave : 0; r < cs.wr; r += split) {
+            const int y = r - (p - 1) + 16 * ba + m;
+            const bool ok = y >= 0 && y < PC_TY;
+            const float* wrow = Wl + r * cs.wc + acol;
+            const float* urow = Ul + r * cs.wc + acol;
+            const float* trow = Tl + (ok ? y : 0) * PC_TS + kk;
+            const float* rrow = Rl + (ok ? y : 0) * PC_TS + kk;
+#pragma unroll 8
+            for (int x0 = 0; x0 < PC_TX; x0 += 4) {
+                const float tb = ok ? trow[x0] : 0.0f, rb = ok ? rrow[x0] : 0.0f;
+                c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wrow[x0], tb, c0, 0, 0, 0);
+                c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(urow[x0], rb, c1, 0, 0, 0);
             }
         }
-        if (cs.items >= kBlock) {
-            // one row group: write straight to the running partial
-            for (int i = 0; i < PC_RB; ++i) {
-                const int q = ch * PC_RB + i;
-                if (q < p) part[(size_t)blockIdx.x * p * p + a * p + q] += (double)acc[i];
-            }
+        c0 += c1;
+        double* out = part + (size_t)blockIdx.x * p * p;
+        if (split > 1) {
+            __syncthreads();  // the windows are no longer read: reuse LDS for the waves' sums
+#pragma unroll
+            for (int i = 0; i < 4; ++i) smem[wave * 256 + (4 * kk + i) * 16 + m] = c0[i];
+            __syncthreads();
+            const int q = threadIdx.x >> 4, a = threadIdx.x & 15;
+            float sum = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kBlock / 64; ++w) sum += smem[w * 256 + threadIdx.x];
+            if (q < p && a < p) out[a * p + q] += (double)sum;
         } else {
-            a_it = a;
-            c_it = ch;
-            yg_it = yg;
-        }
-    }
-    if (cs.items < kBlock) {
-        __syncthreads();  // the windows are no longer read: reuse LDS for the row-group sums
-        float* rs = smem;  // [yg][p*p]
-        if (a_it >= 0)
-            for (int i = 0; i < PC_RB; ++i) {
-                const int q = c_it * PC_RB + i;
-                if (q < p) rs[yg_it * p * p + a_it * p + q] = acc[i];
+            const int a = 16 * ba + m;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int q = 16 * bq + 4 * kk + i;
+                if (q < p && a < p) out[a * p + q] += (double)c0[i];
             }
-        __syncthreads();
-        for (int l = threadIdx.x; l < p * p; l += kBlock) {
-            float s = 0.0f;
-            for (int g = 0; g < cs.yg; ++g) s += rs[g * p * p + l];
-            part[(size_t)blockIdx.x * p * p + l] += (double)s;
         }
+        if (split > 1) break;
     }
     const double d = block_sum(dot, red);
     if (threadIdx.x == 0) apart[blockIdx.x] -= d;
