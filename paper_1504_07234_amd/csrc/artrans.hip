@@ -28,6 +28,7 @@
 #include "artrans.hpp"
 #include "common.hpp"
 #include "fft_core.hpp"
+#include "fft_seq.hpp"
 #include "kernels.hpp"
 
 namespace mlba {

@@ -21,7 +21,8 @@ constexpr int kFixedM2 = 1152;  // the FFT-blur grid of ~1K images (unknowns of 
 constexpr int FFT_MAX_ELEMS = FFT_EPT * kBlock;  // complex values per workgroup (16 KB of LDS)
 
 // n = 2^a 3^b 5^c: a Stockham plan of n itself; otherwise the Bluestein form
-// over bluestein_len(n), the smallest such length >= 2n - 1.
+// over bluestein_len(n), the smallest power of two >= 2n - 1 (and 64), whose
+// transforms are compiled (fft_seq.hpp).
 __host__ __device__ constexpr bool smooth235(int n) {
     if (n < 1) return false;
     while (n % 2 == 0) n /= 2;
@@ -31,8 +32,8 @@ __host__ __device__ constexpr bool smooth235(int n) {
 }
 
 __host__ __device__ constexpr int bluestein_len(int n) {
-    int m = 2 * n - 1;
-    while (!smooth235(m)) ++m;
+    int m = 64;
+    while (m < 2 * n - 1) m *= 2;
     return m;
 }
 
@@ -373,55 +374,10 @@ __device__ __forceinline__ void lds_stockham(float2* buf, int len, const FftDesc
 }
 
 // Length-n DFT of the one sequence in buf[0, n) by Bluestein's identity
-// jk = (j^2 + k^2 - (k - j)^2) / 2:
-//   X_k = c_k sum_j (x_j c_j) conj(c_{k-j}),  c_k = exp(-i pi k^2 / n),
-// the sum a circular convolution of length m >= 2n - 1 done with two m-point
-// transforms and the stored spectrum of conj(c) (scaled by 1/m).  The inverse
-// direction is conj(DFT(conj x)).  buf holds m slots; every thread of the
-// workgroup takes part (m <= FFT_MAX_ELEMS).
-template <int DIR, int EPT = FFT_EPT>
-__device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __restrict__ tw) {
-    constexpr int KE = FFT_MAX_ELEMS / kBlock;
-    const int n = fd.n, m = fd.m;
-    const float2* __restrict__ chirp = tw + m;
-    const float2* __restrict__ bspec = tw + m + n;
-    float2 a[KE];
-#pragma unroll
-    for (int j = 0; j < KE; ++j) {
-        const int k = (int)threadIdx.x + j * kBlock;
-        a[j] = make_float2(0.0f, 0.0f);
-        if (k < n) {
-            float2 x = buf[lds_slot(k)];
-            if (DIR > 0) x.y = -x.y;
-            a[j] = cmul(x, chirp[k]);
-        }
-    }
-    __syncthreads();  // every x read before the zero padding overwrites it
-#pragma unroll
-    for (int j = 0; j < KE; ++j) {
-        const int k = (int)threadIdx.x + j * kBlock;
-        if (k < m) buf[lds_slot(k)] = a[j];
-    }
-    __syncthreads();
-    lds_stockham<-1, EPT>(buf, m, fd, 1, 8, tw);
-#pragma unroll
-    for (int j = 0; j < KE; ++j) {
-        const int k = (int)threadIdx.x + j * kBlock;
-        if (k < m) buf[lds_slot(k)] = cmul(buf[lds_slot(k)], bspec[k]);
-    }
-    __syncthreads();
-    lds_stockham<1, EPT>(buf, m, fd, 1, 8, tw);
-#pragma unroll
-    for (int j = 0; j < KE; ++j) {
-        const int k = (int)threadIdx.x + j * kBlock;
-        if (k < n) {
-            float2 v = cmul(buf[lds_slot(k)], chirp[k]);
-            if (DIR > 0) v.y = -v.y;
-            buf[lds_slot(k)] = v;
-        }
-    }
-    __syncthreads();
-}
+// (fft_seq.hpp); buf holds m slots, every thread of the workgroup takes part
+// (m <= FFT_MAX_ELEMS).
+template <int DIR>
+__device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __restrict__ tw);
 
 // run-time 2/3/5-smooth lengths
 template <int DIR, int EPT = FFT_EPT>
@@ -718,7 +674,7 @@ __device__ __forceinline__ void lds_fft_any(float2* buf, const FftDesc& fd, int 
     if constexpr (NT > 0) {
         lds_fft_fixed<DIR, NT>(buf, tw, pre);
     } else if constexpr (NT == kAnyLen) {
-        if (fd.m > 0) lds_bluestein<DIR, EPT>(buf, fd, tw);  // one sequence per workgroup
+        if (fd.m > 0) lds_bluestein<DIR>(buf, fd, tw);  // one sequence per workgroup
         else lds_fft<DIR, EPT>(buf, fd, nseq, seq_shift, tw);
     } else {
         lds_fft<DIR, EPT>(buf, fd, nseq, seq_shift, tw);

@@ -195,6 +195,77 @@ __device__ __forceinline__ void seq_sync_all() {
     else seq_sync<N>();
 }
 
+// ---- Bluestein form ----------------------------------------------------------
+
+// Length-n DFT of the one sequence in buf[0, n) by Bluestein's identity
+// jk = (j^2 + k^2 - (k - j)^2) / 2:
+//   X_k = c_k sum_j (x_j c_j) conj(c_{k-j}),  c_k = exp(-i pi k^2 / n),
+// the sum a circular convolution of length M >= 2n - 1 done with two M-point
+// transforms and the stored spectrum of conj(c) (scaled by 1/M).  The inverse
+// direction is conj(DFT(conj x)).  The sequence's M / 8 threads do the work:
+// within one wave the other waves wait at the end, above that they repeat it
+// (the same values to the same slots) to keep the barriers.  A pass is bound by
+// the latency of its chain of stages: on the run-time plan of the smallest
+// 2^a 3^b 5^c >= 2n - 1 each of them had a table read, run-time strides and two
+// barriers.  P at n = 66 / 226 / 514 / 1022, BCCB: 41 / 43 / 65 / 67 -> 19 / 21 /
+// 33 / 40 us; antireflective n = 196 / 500: 50 / 86 -> 30 / 35 us.  M is a power of
+// two also where 3 2^a or 5-smooth is shorter (n = 66: m = 135 -> 256, 514:
+// 1080 -> 2048): the longer compiled chain is still half the run-time plan's.
+template <int DIR, int M>
+__device__ __forceinline__ void seq_bluestein(float2* buf, int n, const float2* __restrict__ tw) {
+    using Q = Seq<M>;
+    const float2* __restrict__ chirp = tw + M;
+    const float2* __restrict__ bspec = tw + M + n;
+    const int t = threadIdx.x & (Q::T - 1);
+    if (Q::T > 64 || threadIdx.x < 64) {
+        Q q;
+        q.load_tw(tw, t);
+        float2 v[8], c[8], u[Q::BL][Q::RL], b[Q::BL][Q::RL], co[Q::BL][Q::RL];
+        Q::inputs(t, [&](int r, int k) {
+            c[r] = k < n ? chirp[k] : make_float2(0.0f, 0.0f);
+            v[r] = k < n ? buf[lds_slot(k)] : make_float2(0.0f, 0.0f);
+        });
+        Q::outputs(t, [&](int i, int r, int k) {
+            b[i][r] = bspec[k];
+            co[i][r] = k < n ? chirp[k] : make_float2(0.0f, 0.0f);
+        });
+        Q::inputs(t, [&](int r, int) {
+            if (DIR > 0) v[r].y = -v[r].y;
+            v[r] = cmul(v[r], c[r]);
+        });
+        seq_sync<M>();  // every x read before the transform's stages overwrite it
+        q.template run<-1>(v, u, buf, t);
+        Q::outputs(t, [&](int i, int r, int) { u[i][r] = cmul(u[i][r], b[i][r]); });
+        seq_sync<M>();
+        Q::put(u, buf, t);
+        seq_sync<M>();
+        Q::inputs(t, [&](int r, int k) { v[r] = buf[lds_slot(k)]; });
+        seq_sync<M>();
+        q.template run<1>(v, u, buf, t);
+        seq_sync<M>();
+        Q::outputs(t, [&](int i, int r, int k) {
+            if (k < n) {
+                float2 x = cmul(u[i][r], co[i][r]);
+                if (DIR > 0) x.y = -x.y;
+                buf[lds_slot(k)] = x;
+            }
+        });
+    }
+    __syncthreads();
+}
+
+template <int DIR>
+__device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __restrict__ tw) {
+    switch (fd.m) {
+        case 64: return seq_bluestein<DIR, 64>(buf, fd.n, tw);
+        case 128: return seq_bluestein<DIR, 128>(buf, fd.n, tw);
+        case 256: return seq_bluestein<DIR, 256>(buf, fd.n, tw);
+        case 512: return seq_bluestein<DIR, 512>(buf, fd.n, tw);
+        case 1024: return seq_bluestein<DIR, 1024>(buf, fd.n, tw);
+        default: return seq_bluestein<DIR, 2048>(buf, fd.n, tw);
+    }
+}
+
 // ---- BCCB passes: THREADS / seq_threads(N) sequences per workgroup -----------
 
 // row pairs -> T[k][row], k = 0 .. N/2; pair0: the workgroup's first pair.

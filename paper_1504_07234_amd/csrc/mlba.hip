@@ -79,16 +79,20 @@ std::vector<float2> fft_table(const FftDesc& d) {
             ci[k] = sin(ang);
             t[len + k] = make_float2((float)cr[k], (float)ci[k]);
         }
+        std::vector<double> wr(m), wi(m);
+        for (int e = 0; e < m; ++e) {
+            const double ang = -2.0 * pi * (double)e / (double)m;
+            wr[e] = cos(ang);
+            wi[e] = sin(ang);
+        }
         // b_k = conj(c_k) at k and m - k (|k| < n), zero elsewhere
         for (int q = 0; q < m; ++q) {
             double sr = 0.0, si = 0.0;
             for (int k = -(n - 1); k <= n - 1; ++k) {
                 const int kk = k < 0 ? -k : k;
                 const long long e = ((long long)q * ((k + m) % m)) % m;
-                const double ang = -2.0 * pi * (double)e / (double)m;
-                const double wr = cos(ang), wi = sin(ang);
-                sr += cr[kk] * wr + ci[kk] * wi;  // conj(c) * w
-                si += cr[kk] * wi - ci[kk] * wr;
+                sr += cr[kk] * wr[e] + ci[kk] * wi[e];  // conj(c) * w
+                si += cr[kk] * wi[e] - ci[kk] * wr[e];
             }
             t[len + n + q] = make_float2((float)(sr / m), (float)(si / m));
         }

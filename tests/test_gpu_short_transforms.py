@@ -31,6 +31,25 @@ def test_apply_p(n, kind):
     assert np.linalg.norm(t - ref) <= TOL * np.linalg.norm(ref)
 
 
+# Bluestein form over m = 64 .. 2048: per axis four m-point transforms of at
+# most 11 levels and six products; the spectrum of the chirp is flat to within a
+# factor of 2.
+BLUE_TOL = 2 * 2 * (4 * 11 + 6) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("kind", [mlba.BCCB, mlba.DCT])
+@pytest.mark.parametrize("n", [14, 22, 34, 62, 66, 126, 130, 226, 254, 258, 510, 514, 1022])
+def test_apply_p_bluestein(n, kind):
+    g = np.random.Generator(np.random.PCG64(n))
+    h = g.uniform(0.0, 1.0, (5, 5))
+    h = (h / h.sum()).astype(np.float32)
+    r = g.standard_normal((n, n)).astype(np.float32)
+    with mlba.Plan(n, 5, mlba.RECT, kind, 1, torch.as_tensor(h).cuda()) as plan:
+        t = plan.apply_P(torch.as_tensor(r).cuda(), 1.0).double().cpu().numpy()
+    ref = opc.apply(r.astype(np.float64), h.astype(np.float64), 1.0, kind)
+    assert np.linalg.norm(t - ref) <= BLUE_TOL * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("n,kind", [(64, mlba.BCCB), (96, mlba.DCT), (256, mlba.BCCB), (768, mlba.DCT)])
 def test_norms_from_the_column_pass(n, kind):
     """||r^k|| summed inside P's column pass equals the separate sum's, which a
