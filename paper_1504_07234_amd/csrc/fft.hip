@@ -42,15 +42,18 @@ __device__ __forceinline__ void fft_rows_r2c_body_f(Src src, int n_, float2* __r
     const int row0 = blk * 2 * G;
     FixedTw<(NT > 0 ? NT : 1)> twp;
     if constexpr (NT > 0) fixed_tw_load<NT>(tw, twp.w);
-    strided_copy<NT, float2>(
-        G * n,
-        [&](int idx) {
-            const int g = idx / n;
-            const int x = idx - g * n;
-            const size_t ra = (size_t)(row0 + 2 * g) * n;
-            return make_float2(src(ra + x), src(ra + n + x));
-        },
-        [&](int idx, float2 v) { buf[lds_slot(idx)] = v; });
+    struct Pair {
+        typename Src::Raw a, b;
+    };
+    const auto at = [&](int idx) {
+        const int g = idx / n;
+        return (size_t)(row0 + 2 * g) * n + (idx - g * n);
+    };
+    strided_copy<NT, Pair>(
+        G * n, [&](int idx) { return Pair{src.load(at(idx)), src.load(at(idx) + n)}; },
+        [&](int idx, Pair v) {
+            buf[lds_slot(idx)] = make_float2(src.value(at(idx), v.a), src.value(at(idx) + n, v.b));
+        });
     __syncthreads();
     lds_fft_any<-1, NT>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     const int half = n / 2 + 1;
@@ -70,7 +73,7 @@ template <int NT = 0>
 __device__ __forceinline__ void fft_rows_r2c_body(const float* __restrict__ src, int n_, float2* __restrict__ T,
                                                   int ts, const FftDesc& fd, const float2* __restrict__ tw, int G_,
                                                   int seq_shift, int blk, float2* buf) {
-    fft_rows_r2c_body_f<NT>([&](size_t i) { return src[i]; }, n_, T, ts, fd, tw, G_, seq_shift, blk, buf);
+    fft_rows_r2c_body_f<NT>(RowSource{src}, n_, T, ts, fd, tw, G_, seq_shift, blk, buf);
 }
 
 // CC rows of T per workgroup, along the column index:
@@ -605,14 +608,28 @@ __global__ __launch_bounds__(kBlock) void fft_cols_residual_kernel(float2* __res
 // to the rows it reads and transforms the new res; the inverse row pass
 // writes z = P res with the partial sums of res . z per workgroup.  The
 // arithmetic of every value is that of the separate update and dot kernels.
-// the update of Algorithm 2's vectors at flat index i
-__device__ __forceinline__ float pcg_row_value(const PcgVec& v, bool on, float a, size_t i) {
-    if (!on) return v.res[i];
-    v.t[i] = fmaf(a, v.d[i], v.t[i]);
-    const float r = fmaf(-a, v.q[i], v.res[i]);
-    v.res[i] = r;
-    return r;
-}
+// The update of Algorithm 2's vectors at flat index i.  Bound by memory (six
+// vectors); with each element's stores in front of the next one's loads a row
+// was a chain of round trips: 16.7 -> 9.0 us at 1024 x 1024.
+struct PcgSource {
+    struct Raw {
+        float t, d, q, res;
+    };
+    const PcgVec& v;
+    bool on;
+    float a;
+    __device__ __forceinline__ Raw load(size_t i) const {
+        if (!on) return Raw{0.0f, 0.0f, 0.0f, v.res[i]};
+        return Raw{v.t[i], v.d[i], v.q[i], v.res[i]};
+    }
+    __device__ __forceinline__ float value(size_t i, const Raw& x) const {
+        if (!on) return x.res;
+        v.t[i] = fmaf(a, x.d, x.t);
+        const float r = fmaf(-a, x.q, x.res);
+        v.res[i] = r;
+        return r;
+    }
+};
 
 template <int NT>
 __global__ __launch_bounds__(kBlock) void pcg_rows_r2c_kernel(int n, float2* __restrict__ T, int ts, FftDesc fd,
@@ -622,8 +639,7 @@ __global__ __launch_bounds__(kBlock) void pcg_rows_r2c_kernel(int n, float2* __r
     const bool on = *v.act != 0.0;
     const float a = on ? (float)(*v.rho / *v.pq) : 0.0f;
     fft_rows_r2c_body_f<NT>(
-        [&](size_t i) { return pcg_row_value(v, on, a, i); },
-        n, T, ts, fd, tw, G, seq_shift, xcd_block(blockIdx.x, gridDim.x), buf);
+        PcgSource{v, on, a}, n, T, ts, fd, tw, G, seq_shift, xcd_block(blockIdx.x, gridDim.x), buf);
 }
 
 template <int NT>
@@ -727,7 +743,7 @@ __global__ __launch_bounds__(seq_block(N)) void fft_rows_r2c_seq_kernel(const fl
                                                                         float2* __restrict__ T, int ts,
                                                                         const float2* __restrict__ tw) {
     extern __shared__ float2 buf[];
-    seq_rows_r2c<N, seq_block(N)>([&](size_t i) { return src[i]; }, T, ts, tw, xcd_block(blockIdx.x, gridDim.x), buf);
+    seq_rows_r2c<N, seq_block(N)>(RowSource{src}, T, ts, tw, xcd_block(blockIdx.x, gridDim.x), buf);
 }
 
 // red_out: as in fft_cols_kernel
@@ -777,8 +793,7 @@ __global__ __launch_bounds__(seq_block(N)) void pcg_rows_r2c_seq_kernel(float2* 
     extern __shared__ float2 buf[];
     const bool on = *v.act != 0.0;
     const float a = on ? (float)(*v.rho / *v.pq) : 0.0f;
-    seq_rows_r2c<N, seq_block(N)>([&](size_t i) { return pcg_row_value(v, on, a, i); }, T, ts, tw,
-                                  xcd_block(blockIdx.x, gridDim.x), buf);
+    seq_rows_r2c<N, seq_block(N)>(PcgSource{v, on, a}, T, ts, tw, xcd_block(blockIdx.x, gridDim.x), buf);
 }
 
 template <int N>
@@ -1227,7 +1242,7 @@ __device__ __forceinline__ void precond_seq_pass(const BatchImage& I, float inv,
     float* Tr = (float*)(void*)I.swork;
     if constexpr (PRECOND == 0) {
         if (PASS == 0)
-            seq_rows_r2c<N, kBlock>([r = I.r](size_t i) { return r[i]; }, T, I.ts, I.tw, blk, buf);
+            seq_rows_r2c<N, kBlock>(RowSource{I.r}, T, I.ts, I.tw, blk, buf);
         if (PASS == 1)
             seq_cols<N, kBlock>(T, I.ts, I.spec, I.alpha, inv, I.tw, blk, buf, nullptr, I.sstore, I.sfwd, I.eacc);
         if (PASS == 2) seq_rows_c2r<N, kBlock>(T, I.ts, [t = I.t](size_t i, float v) { t[i] = v; }, I.tw, blk, buf);

@@ -99,6 +99,14 @@ __device__ __forceinline__ void strided_copy(int count, Fetch fetch, Put put, in
     }
 }
 
+// The values of a row pass as they lie in memory.
+struct RowSource {
+    using Raw = float;
+    const float* src;
+    __device__ __forceinline__ Raw load(size_t i) const { return src[i]; }
+    __device__ __forceinline__ float value(size_t, Raw x) const { return x; }
+};
+
 // Sum of p[i] over i = threadIdx.x, threadIdx.x + kBlock, ... < count, added
 // in that order (the order of a plain strided loop); four loads in flight at
 // a time.

@@ -269,7 +269,8 @@ __device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __re
 // ---- BCCB passes: THREADS / seq_threads(N) sequences per workgroup -----------
 
 // row pairs -> T[k][row], k = 0 .. N/2; pair0: the workgroup's first pair.
-// src(i): the value at flat index i of the N x N input (read once per element).
+// src.load(i), src.value(i, loaded): the value at flat index i of the N x N input
+// (each called once per element, every load of a thread before its first value).
 template <int N, int THREADS, class Src>
 __device__ __forceinline__ void seq_rows_r2c(Src src, float2* __restrict__ T, int ts, const float2* __restrict__ tw,
                                              int blk, float2* lds) {
@@ -282,7 +283,14 @@ __device__ __forceinline__ void seq_rows_r2c(Src src, float2* __restrict__ T, in
     if (2 * (pair0 + g) < N) {
         float2 v[8], u[Seq<N>::BL][Seq<N>::RL];
         const size_t ra = (size_t)2 * (pair0 + g) * N;
-        Seq<N>::inputs(t, [&](int r, int x) { v[r] = make_float2(src(ra + x), src(ra + N + x)); });
+        typename Src::Raw a[8], b[8];
+        Seq<N>::inputs(t, [&](int r, int x) {
+            a[r] = src.load(ra + x);
+            b[r] = src.load(ra + N + x);
+        });
+        Seq<N>::inputs(t, [&](int r, int x) {
+            v[r] = make_float2(src.value(ra + x, a[r]), src.value(ra + N + x, b[r]));
+        });
         q.template run<-1>(v, u, buf, t);
         seq_sync<N>();
         Seq<N>::put(u, buf, t);

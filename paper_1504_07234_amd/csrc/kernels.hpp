@@ -508,7 +508,9 @@ hipError_t launch_pcg_dir(float* d, const float* z, size_t count, const double* 
 hipError_t launch_pcg_begin(double* st, int* hist, hipStream_t s);
 hipError_t launch_pcg_check(double* st, const double* rn, int j, int max_steps, double tol, int* hist,
                             hipStream_t s);
-hipError_t launch_axpy(float* y, const float* x, size_t count, float a, hipStream_t s);  // y += a x
+// y += a x, partial sums of x . y (the new y)
+hipError_t launch_axpy_dot(float* y, const float* x, size_t count, float a, double* partials, int* n_partials,
+                           hipStream_t s);
 // w -= ab[0] v + sqrt(*beta2) vprev (vprev may be null), partial sums of w^2
 hipError_t launch_lanczos_step(float* w, const float* v, const float* vprev, size_t count, const double* ab,
                                const double* beta2, double* partials, int* n_partials, hipStream_t s);

@@ -593,8 +593,7 @@ int do_gram(mlba_plan_s* P, float* d, float* q, double alpha, int* np, const Pcg
     }
     STCHK(do_blurT(P, d, P->w, s));
     STCHK(do_blur(P, P->w, nullptr, q, false, nullptr, false, s));
-    HIPCHK(launch_axpy(q, d, nn, (float)alpha, s));
-    HIPCHK(launch_dot_partials(d, q, nn, P->partials, np, s));
+    HIPCHK(launch_axpy_dot(q, d, nn, (float)alpha, P->partials, np, s));
     return MLBA_OK;
 }
 

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import alg2 as oa2
 from oracle import precond as opc
 from paper_1504_07234_amd import mlba
 
@@ -63,3 +64,23 @@ def test_norms_from_the_column_pass(n, kind):
         f2, b = plan.restore(y, alpha=0.1, delta=0.2, iters=6, implicit=True, stop=(0.0, 1.0, 1))
     assert torch.equal(f1, f2)
     assert np.allclose(a.rnorm, b.rnorm, rtol=1e-13)
+
+
+@pytest.mark.parametrize("n", [48, 64, 512, 514, 1000, 1024])
+def test_algorithm2_vectors(n):
+    """The PCG's vector updates inside P's row passes and in the sum of q . d: run-time,
+    compiled and Bluestein plans; n^2 below, at and above one element per thread.
+    Same steps and the bound of the other comparisons with the oracle, 1e-4."""
+    g = np.random.Generator(np.random.PCG64(n + 2))
+    h = g.uniform(0.5, 1.0, (5, 5))
+    h = (h / h.sum()).astype(np.float32)
+    y = g.uniform(0.0, 1.0, (n, n)).astype(np.float32)
+    iters, steps = 2, 3
+    ref = oa2.alg2(y.astype(np.float64), h.astype(np.float64), mlba.RECT, mlba.BCCB, 1, np.full(iters, 0.1),
+                   np.full(iters + 1, 0.8), 1e-3, iters, beta_max=steps, tol=1e-12)
+    with mlba.Plan(n, 5, mlba.RECT, mlba.BCCB, 1, torch.as_tensor(h).cuda()) as plan:
+        f, info = plan.restore(torch.as_tensor(y).cuda(), alpha=0.1, mu=1e-3, delta=0.8, iters=iters,
+                               method=mlba.ALG2, pcg=(steps, 1e-12))
+        f = f.double().cpu().numpy()
+    assert info.pcg_steps == ref["betas"].tolist()
+    assert np.linalg.norm(f - ref["f"]) <= 1e-4 * np.linalg.norm(ref["f"])
