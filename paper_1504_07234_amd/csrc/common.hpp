@@ -67,6 +67,18 @@ __device__ __forceinline__ float fetch_antireflect(const float* __restrict__ src
     return wya * (wxa * ra[xa] + wxb * ra[xb]) + wyb * (wxa * rb[xa] + wxb * rb[xb]);
 }
 
+// Source index of position x of an axis under a single-source extension, and
+// whether it has one (zero extension); positions further out than the pad feed
+// no output and are clamped into the image.
+__device__ __forceinline__ int ext_axis(int x, int S, int ext, bool* has) {
+    *has = ext != EXT_ZERO || (x >= 0 && x < S);
+    const bool lo = x < 0, hi = x >= S;
+    const int per = lo ? x + S : (hi ? x - S : x);
+    const int ref = lo ? -1 - x : (hi ? 2 * S - 1 - x : x);
+    const int s = ext == EXT_PERIODIC ? per : ref;
+    return min(max(s, 0), S - 1);
+}
+
 // Read src[y][x] of an S x S image under extension `ext`.
 __device__ __forceinline__ float fetch_ext(const float* __restrict__ src, int S, int y, int x, int ext) {
     if (y >= 0 && y < S && x >= 0 && x < S) return src[(size_t)y * S + x];

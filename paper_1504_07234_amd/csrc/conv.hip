@@ -119,18 +119,6 @@ struct __attribute__((packed, aligned(4))) FloatQuad {
     float v[4];
 };
 
-// Source index of position x of an axis under a single-source extension, and
-// whether it has one (zero extension); positions further out than the pad feed
-// no output and are clamped into the image.
-__device__ __forceinline__ int conv_axis(int x, int S, int ext, bool* has) {
-    *has = ext != EXT_ZERO || (x >= 0 && x < S);
-    const bool lo = x < 0, hi = x >= S;
-    const int per = lo ? x + S : (hi ? x - S : x);
-    const int ref = lo ? -1 - x : (hi ? 2 * S - 1 - x : x);
-    const int s = ext == EXT_PERIODIC ? per : ref;
-    return min(max(s, 0), S - 1);
-}
-
 // Splits four values into the rows of the window; chk collects what is left
 // below the second part, which is NaN unless the value is finite in bfloat16.
 template <int C>
@@ -177,11 +165,11 @@ __device__ __forceinline__ void conv_fetch(const ConvJob& j, int P, int TY, int 
         int xi[4];
         bool hx[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) xi[e] = conv_axis(x0 + lx + e, S, ext, &hx[e]);
+        for (int e = 0; e < 4; ++e) xi[e] = ext_axis(x0 + lx + e, S, ext, &hx[e]);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             bool hy;
-            const float* row = j.src + (size_t)conv_axis(y0 + min(ly0 + u * RS, rows - 1), S, ext, &hy) * S;
+            const float* row = j.src + (size_t)ext_axis(y0 + min(ly0 + u * RS, rows - 1), S, ext, &hy) * S;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float q = row[xi[e]];
