@@ -41,6 +41,7 @@ struct mlba_batch_s {
     int* maps = nullptr;  // one device buffer holding every map
     size_t maps_cap = 0;  // its size in ints: the largest over every tile choice
     Map conv_a, conv_at, tap_a, tap_at, fold, fill, pre[3], syn[5], ana[5], low[5], shr[5], fill_om;
+    bool syn_wide[5] = {};  // of syn
     // tile choices (set by mlba_batch_autotune)
     int conv_ry[2] = {1, 1};          // output rows per thread of the A and A^T launches
     int rows_want = 0, cols_want = 0;  // transform batching caps (0: built-in choice per size)
@@ -139,7 +140,9 @@ int configure(mlba_batch_s* B, hipStream_t s, bool dry_run = false, size_t* ints
         add(B->pre[pass], t);
     }
     for (int lev = 1; lev <= B->levels; ++lev) {
-        for (int i = 0; i < count; ++i) t[i] = synthesis_level_tiles(B->host[i].N, 1 << (lev - 1));
+        B->syn_wide[lev] = synthesis_wide(B->host.data(), count, 1 << (lev - 1));
+        for (int i = 0; i < count; ++i)
+            t[i] = synthesis_level_tiles(B->host[i].N, 1 << (lev - 1), B->syn_wide[lev]);
         add(B->syn[lev], t);
         for (int i = 0; i < count; ++i) t[i] = analysis_level_tiles(B->host[i].N, 1 << (lev - 1));
         add(B->ana[lev], t);
@@ -213,7 +216,7 @@ int enqueue(mlba_batch_s* B, int iters, bool fill_state, bool implicit, hipStrea
     for (int k = 0; k < iters; ++k) {
         for (int lev = B->levels; lev >= 1; --lev) {
             const Map& m = B->syn[lev];
-            HIPCHK(launch_synthesis_batched(I, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 0, s));
+            HIPCHK(launch_synthesis_batched(I, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), B->syn_wide[lev], 0, s));
         }
         HIPCHK(launch_tapconv_batched(I, B->tap_a.bmap, B->tap_a.bfirst, B->tap_a.nblocks, 1, B->pmax, 0, B->partials,
                                       s));
@@ -232,7 +235,7 @@ int enqueue(mlba_batch_s* B, int iters, bool fill_state, bool implicit, hipStrea
     }
     for (int lev = B->levels; lev >= 1; --lev) {
         const Map& m = B->syn[lev];
-        HIPCHK(launch_synthesis_batched(I, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 1, s));
+        HIPCHK(launch_synthesis_batched(I, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), B->syn_wide[lev], 1, s));
     }
     return MLBA_OK;
 }

@@ -7,12 +7,17 @@
 // Analysis + Bregman update: one thread per column and 8-row strip, no LDS;
 // the x-direction taps at x-d and x+d are read from memory (cache hits) and
 // every old coefficient of the strip is loaded before the first store.
-// Synthesis: one thread per column of an 8-row strip; a workgroup covers 256
-// - 2d output columns plus a d-column halo on each side.  Every thread
+// Synthesis: one thread per column of an 8-row strip; a workgroup covers 256 - 2d
+// or 64 - 2d output columns plus a d-column halo on each side.  Every thread
 // streams its column of each of the 9 inputs (8 + 2d rows, coalesced across
 // the wavefront) through registers, applies the y-direction transposes there,
-// parks the three partial sums in LDS and, after one barrier, applies the
-// x-direction transposes for the interior columns.
+// parks the three partial sums in LDS and applies the x-direction transposes
+// for the interior columns.
+// Both are bound by memory, or by its latency on images that do not fill the
+// chip.  With 256 columns to a workgroup an image of 270 columns (256 x 256, p =
+// 15) takes two of them, the second for 16 columns, and 16 images' strips load
+// the 256 CUs unevenly; with one wave to a workgroup a level of these takes 15 to
+// 16 us instead of 19 to 21 (analysis), 12.7 instead of 14.4 (synthesis).
 //
 // The transpose (synthesis) uses the fact that for a symmetric mask the
 // reflective operator's transpose is the mirrored mask applied to the
@@ -25,6 +30,9 @@
 #include "kernels.hpp"
 
 namespace mlba {
+
+constexpr int WAVE = 64;
+// Columns (threads) of an analysis or synthesis workgroup: W = kBlock, or WAVE.
 
 // Analysis of one level: one thread per column, AN_TY rows per thread.  The
 // x-direction filters read the two neighbouring columns straight from memory
@@ -66,11 +74,11 @@ __device__ __forceinline__ void analysis_yfilter(const float* h0, const float* h
 
 // Old coefficients come from zin_lev / low_in (the same arrays as zlev / low
 // for an in-place update; a new state slot otherwise).
-template <int D>
+template <int D, int W>
 __device__ __forceinline__ void analysis_tile(const float* __restrict__ v, int N, const float* zin_lev,
                                               const float* low_in, float* zlev, float* low, int accum_bands,
                                               int accum_low, int bx, int by) {
-    const int x = bx * kBlock + threadIdx.x;
+    const int x = bx * W + threadIdx.x;
     const int y0 = by * AN_TY;
     if (x >= N) return;
     const size_t NN = (size_t)N * N;
@@ -116,7 +124,7 @@ __global__ __launch_bounds__(kBlock) void analysis_level_kernel(const float* __r
                                                                 int accum_bands, int accum_low) {
     int bx, by;
     xcd_tile(&bx, &by);  // row halos of adjacent strips in one L2
-    analysis_tile<D>(v, N, zlev, low, zlev, low, accum_bands, accum_low, bx, by);
+    analysis_tile<D, kBlock>(v, N, zlev, low, zlev, low, accum_bands, accum_low, bx, by);
 }
 
 // Reverse-sweep level: the filters of analysis_tile, and for every band value
@@ -184,12 +192,20 @@ __device__ __forceinline__ void analysis_adjoint_tile(const float* __restrict__ 
     }
 }
 
-template <int D>
+// Columns of inputs in flight per thread of a one-wave workgroup: the nine where
+// they fit some 108 registers, which leaves three waves per SIMD.  Waited for one
+// by one they were nine round trips.  Large images have more waves instead.
+__host__ __device__ constexpr int syn_ahead(int d, int w) {
+    const int k = w == WAVE ? 108 / (FR_TY + 2 * d) : 1;
+    return k < 9 ? k : 9;
+}
+
+template <int D, int W>
 __device__ __forceinline__ void synthesis_tile(const float* __restrict__ zlev, const float* __restrict__ low,
                                                int N, float* __restrict__ out, const LevelMu& mu, float delta,
                                                int thr_low, int thr_bands, int bx, int by,
-                                               float (*ys)[FR_TY][kBlock]) {
-    constexpr int IW = kBlock - 2 * D;
+                                               float (*ys)[FR_TY][W]) {
+    constexpr int IW = W - 2 * D, AHEAD = syn_ahead(D, W);
     const int x0 = bx * IW;
     const int y0 = by * FR_TY;
     const int c = threadIdx.x;
@@ -213,22 +229,31 @@ __device__ __forceinline__ void synthesis_tile(const float* __restrict__ zlev, c
 #pragma unroll
         for (int r = 0; r < FR_TY; ++r) acc[i][r] = 0.0f;
 
+    float cols[AHEAD][FR_TY + 2 * D];  // input b = 3 i + j in slot b % AHEAD
+    auto load = [&](int b) {
+        const float* src = b == 0 ? low : zlev + pair_slot(b / 3, b % 3) * NN;
+#pragma unroll
+        for (int q = 0; q < FR_TY + 2 * D; ++q) cols[b % AHEAD][q] = src[(size_t)rowi[q] * N + gx];
+    };
+    if constexpr (AHEAD > 1) {
+#pragma unroll
+        for (int b = 0; b < AHEAD; ++b) load(b);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const bool is_low = (i == 0 && j == 0);
-            const float* src = is_low ? low : zlev + pair_slot(i, j) * NN;
             const bool thr = is_low ? (thr_low != 0) : (thr_bands != 0);
             const float m = is_low ? mu.low : mu.band[pair_slot(i, j)];
             const float sx = (i == 1 && fx) ? -1.0f : 1.0f;
-            // issue the whole column's loads before using any of them
+            if constexpr (AHEAD == 1) load(3 * i + j);
             float col[FR_TY + 2 * D];
 #pragma unroll
-            for (int q = 0; q < FR_TY + 2 * D; ++q) col[q] = src[(size_t)rowi[q] * N + gx];
-#pragma unroll
             for (int q = 0; q < FR_TY + 2 * D; ++q) {
-                float val = col[q];
+                float val = cols[(3 * i + j) % AHEAD][q];
                 if (thr) val = shrink(val, m, delta);
                 const float sy = (j == 1 && rowf[q]) ? -1.0f : 1.0f;
                 col[q] = sx * sy * val;
@@ -241,6 +266,11 @@ __device__ __forceinline__ void synthesis_tile(const float* __restrict__ zlev, c
                 else if (j == 1) acc[i][r] = fmaf(kB1, wm - wp, acc[i][r]);
                 else acc[i][r] += fmaf(-0.25f, wp + wm, 0.5f * w0);
             }
+            if (AHEAD > 1 && 3 * i + j + AHEAD < 9) {
+                __builtin_amdgcn_sched_barrier(0);
+                load(3 * i + j + AHEAD);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 #pragma unroll
@@ -249,7 +279,7 @@ __device__ __forceinline__ void synthesis_tile(const float* __restrict__ zlev, c
         for (int r = 0; r < FR_TY; ++r) ys[i][r][c] = acc[i][r];
     __syncthreads();
 
-    if (c < D || c >= kBlock - D) return;
+    if (c < D || c >= W - D) return;
     const int x = x0 + c - D;
     if (x >= N) return;
     for (int r = 0; r < FR_TY; ++r) {
@@ -273,15 +303,15 @@ __device__ __forceinline__ void synthesis_tile(const float* __restrict__ zlev, c
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(kBlock) void synthesis_level_kernel(const float* __restrict__ zlev,
+template <int D, int W>
+__global__ __launch_bounds__(W) void synthesis_level_kernel(const float* __restrict__ zlev,
                                                                  const float* __restrict__ low, int N,
                                                                  float* __restrict__ out, LevelMu mu,
                                                                  float delta, int thr_low, int thr_bands) {
-    __shared__ float ys[3][FR_TY][kBlock];
+    __shared__ float ys[3][FR_TY][W];
     int bx, by;
     xcd_tile(&bx, &by);  // row halos of adjacent strips in one L2
-    synthesis_tile<D>(zlev, low, N, out, mu, delta, thr_low, thr_bands, bx, by, ys);
+    synthesis_tile<D, W>(zlev, low, N, out, mu, delta, thr_low, thr_bands, bx, by, ys);
 }
 
 template <int D>
@@ -302,45 +332,69 @@ hipError_t launch_analysis_level(const float* v, int N, int d, float* zlev, floa
     }
 }
 
-template <int D>
+template <int D, int W>
 static hipError_t launch_syn(const float* zlev, const float* low, int N, float* out, LevelMu mu, float delta,
                              int tl, int tb, hipStream_t s) {
-    constexpr int IW = kBlock - 2 * D;
+    constexpr int IW = W - 2 * D;
     dim3 grid((N + IW - 1) / IW, (N + FR_TY - 1) / FR_TY);
-    hipLaunchKernelGGL((synthesis_level_kernel<D>), grid, dim3(kBlock), 0, s, zlev, low, N, out, mu, delta,
+    hipLaunchKernelGGL((synthesis_level_kernel<D, W>), grid, dim3(W), 0, s, zlev, low, N, out, mu, delta,
                        tl, tb);
     return hipGetLastError();
 }
 
 hipError_t launch_synthesis_level(const float* zlev, const float* low, int N, int d, float* out, LevelMu mu,
                                   float delta, int thr_low, int thr_bands, hipStream_t s) {
+    // one wave to a workgroup while 256 columns would give no CU two (64 / 400 / 512
+    // / 640 / 1024 columns, three levels: 17.8 / 18.4 / 20.0 / 23.2 / 35.0 us against
+    // 18.8 / 20.0 / 21.9 / 23.6 / 32.7)
+    const bool wide = synthesis_level_tiles(N, d, true) >= 256;
     switch (d) {
-        case 1: return launch_syn<1>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
-        case 2: return launch_syn<2>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
-        case 4: return launch_syn<4>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
-        case 8: return launch_syn<8>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
+        case 1: return wide ? launch_syn<1, kBlock>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s)
+                            : launch_syn<1, WAVE>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
+        case 2: return wide ? launch_syn<2, kBlock>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s)
+                            : launch_syn<2, WAVE>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
+        case 4: return wide ? launch_syn<4, kBlock>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s)
+                            : launch_syn<4, WAVE>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
+        case 8: return wide ? launch_syn<8, kBlock>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s)
+                            : launch_syn<8, WAVE>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s);
         default: return hipErrorInvalidValue;
     }
 }
 
 // ---- batched levels: workgroup b serves image bmap[b], tile b - bfirst[img] ----
 
-int synthesis_level_tiles(int N, int d) {
-    const int IW = kBlock - 2 * d;
-    return ((N + IW - 1) / IW) * ((N + FR_TY - 1) / FR_TY);
+static int synthesis_columns(int N, int d, bool wide) {  // workgroups of a strip
+    const int IW = (wide ? kBlock : WAVE) - 2 * d;
+    return (N + IW - 1) / IW;
 }
 
-int analysis_level_tiles(int N, int d) { return ((N + kBlock - 1) / kBlock) * ((N + AN_TY - 1) / AN_TY); }
+int synthesis_level_tiles(int N, int d, bool wide) {
+    return synthesis_columns(N, d, wide) * ((N + FR_TY - 1) / FR_TY);
+}
+
+// One-wave workgroups where 256 columns to a workgroup launch a quarter more
+// lanes: at 1038 columns (1.18 of them) the wide ones take 0.93 of the time, at
+// 776 (1.23) 0.97, at 520 (1.33) 1.10, at 270 (1.6) 1.13.
+bool synthesis_wide(const BatchImage* imgs, int count, int d) {
+    double wide = 0.0, wave = 0.0;
+    for (int i = 0; i < count; ++i) {
+        wide += (double)imgs[i].N * synthesis_columns(imgs[i].N, d, true) * kBlock;
+        wave += (double)imgs[i].N * synthesis_columns(imgs[i].N, d, false) * WAVE;
+    }
+    return wide <= 1.25 * wave;
+}
+
+int analysis_level_tiles(int N, int d) { return ((N + WAVE - 1) / WAVE) * ((N + AN_TY - 1) / AN_TY); }
 
 // level `lev` of W^T (delta S_mu(z)) for image I, exactly as the single-image
 // path sequences it: level L reads the thresholded low-pass z_0, lower levels
 // the previous level's output; level 1 writes u (or f for the final image).
-template <int D>
-__global__ __launch_bounds__(kBlock) void synthesis_batched_kernel(const BatchImage* __restrict__ imgs,
+template <int D, int W>
+__global__ __launch_bounds__(W) void synthesis_batched_kernel(const BatchImage* __restrict__ imgs,
                                                                    const int* __restrict__ bmap,
                                                                    const int* __restrict__ bfirst, int lev,
                                                                    int final_out, int thr) {
-    __shared__ float ys[3][FR_TY][kBlock];
+    __shared__ float ys[3][FR_TY][W];
     const int xb = xcd_block(blockIdx.x, gridDim.x);  // adjacent tiles of an image in one L2
     const int im = bmap[xb];
     const BatchImage& I = imgs[im];
@@ -353,16 +407,16 @@ __global__ __launch_bounds__(kBlock) void synthesis_batched_kernel(const BatchIm
     mu.low = I.mu[0];
 #pragma unroll
     for (int q = 0; q < 8; ++q) mu.band[q] = I.mu[1 + 8 * (lev - 1) + q];
-    const int IW = kBlock - 2 * D;
+    const int IW = W - 2 * D;
     const int gx = (I.N + IW - 1) / IW;
     const int local = xb - bfirst[im];
     const int by = local / gx;
-    synthesis_tile<D>(zlev, low, I.N, out, mu, thr ? I.delta : 1.0f, (thr && top) ? 1 : 0, thr, local - by * gx,
+    synthesis_tile<D, W>(zlev, low, I.N, out, mu, thr ? I.delta : 1.0f, (thr && top) ? 1 : 0, thr, local - by * gx,
                       by, ys);
 }
 
 template <int D>
-__global__ __launch_bounds__(kBlock) void analysis_batched_kernel(const BatchImage* __restrict__ imgs,
+__global__ __launch_bounds__(WAVE) void analysis_batched_kernel(const BatchImage* __restrict__ imgs,
                                                                   const int* __restrict__ bmap,
                                                                   const int* __restrict__ bfirst, int lev) {
     const int xb = xcd_block(blockIdx.x, gridDim.x);  // adjacent tiles of an image in one L2
@@ -374,10 +428,10 @@ __global__ __launch_bounds__(kBlock) void analysis_batched_kernel(const BatchIma
     float* low = last ? I.z : ((lev & 1) ? I.tmp1 : I.tmp0);
     float* zlev = I.z + (size_t)(1 + 8 * (lev - 1)) * nn;
     const float* zin_lev = I.zin + (size_t)(1 + 8 * (lev - 1)) * nn;
-    const int gx = (I.N + kBlock - 1) / kBlock;
+    const int gx = (I.N + WAVE - 1) / WAVE;
     const int local = xb - bfirst[im];
     const int by = local / gx;
-    analysis_tile<D>(in, I.N, zin_lev, last ? I.zin : low, zlev, low, 1, last ? 1 : 0, local - by * gx, by);
+    analysis_tile<D, WAVE>(in, I.N, zin_lev, last ? I.zin : low, zlev, low, 1, last ? 1 : 0, local - by * gx, by);
 }
 
 template <int D>
@@ -437,27 +491,34 @@ hipError_t launch_analysis_adjoint_batched(const BatchImage* imgs, const int* bm
     return hipGetLastError();
 }
 
-hipError_t launch_synthesis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
-                                    int lev, int d, int final_out, hipStream_t s, int thr) {
-    if (nblocks <= 0) return hipSuccess;
+template <int W>
+static hipError_t launch_sb(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int lev, int d,
+                            int final_out, int thr, hipStream_t s) {
     switch (d) {
-        case 1: hipLaunchKernelGGL(synthesis_batched_kernel<1>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
-        case 2: hipLaunchKernelGGL(synthesis_batched_kernel<2>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
-        case 4: hipLaunchKernelGGL(synthesis_batched_kernel<4>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
-        case 8: hipLaunchKernelGGL(synthesis_batched_kernel<8>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
+        case 1: hipLaunchKernelGGL((synthesis_batched_kernel<1, W>), dim3(nblocks), dim3(W), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
+        case 2: hipLaunchKernelGGL((synthesis_batched_kernel<2, W>), dim3(nblocks), dim3(W), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
+        case 4: hipLaunchKernelGGL((synthesis_batched_kernel<4, W>), dim3(nblocks), dim3(W), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
+        case 8: hipLaunchKernelGGL((synthesis_batched_kernel<8, W>), dim3(nblocks), dim3(W), 0, s, imgs, bmap, bfirst, lev, final_out, thr); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_synthesis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
+                                    int lev, int d, bool wide, int final_out, hipStream_t s, int thr) {
+    if (nblocks <= 0) return hipSuccess;
+    return wide ? launch_sb<kBlock>(imgs, bmap, bfirst, nblocks, lev, d, final_out, thr, s)
+                : launch_sb<WAVE>(imgs, bmap, bfirst, nblocks, lev, d, final_out, thr, s);
 }
 
 hipError_t launch_analysis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
                                    int lev, int d, hipStream_t s) {
     if (nblocks <= 0) return hipSuccess;
     switch (d) {
-        case 1: hipLaunchKernelGGL(analysis_batched_kernel<1>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev); break;
-        case 2: hipLaunchKernelGGL(analysis_batched_kernel<2>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev); break;
-        case 4: hipLaunchKernelGGL(analysis_batched_kernel<4>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev); break;
-        case 8: hipLaunchKernelGGL(analysis_batched_kernel<8>, dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap, bfirst, lev); break;
+        case 1: hipLaunchKernelGGL(analysis_batched_kernel<1>, dim3(nblocks), dim3(WAVE), 0, s, imgs, bmap, bfirst, lev); break;
+        case 2: hipLaunchKernelGGL(analysis_batched_kernel<2>, dim3(nblocks), dim3(WAVE), 0, s, imgs, bmap, bfirst, lev); break;
+        case 4: hipLaunchKernelGGL(analysis_batched_kernel<4>, dim3(nblocks), dim3(WAVE), 0, s, imgs, bmap, bfirst, lev); break;
+        case 8: hipLaunchKernelGGL(analysis_batched_kernel<8>, dim3(nblocks), dim3(WAVE), 0, s, imgs, bmap, bfirst, lev); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -315,12 +315,14 @@ hipError_t launch_shrink_synthesis_batched(const BatchImage* imgs, const int* bm
 hipError_t launch_shrink_synthesis_level(const float* low, const float* s_in, int N, int d, float* out,
                                          LevelMu mu, float delta, hipStream_t s);
 // batched framelet levels (all images share `levels`); tiles per image:
-int synthesis_level_tiles(int N, int d);
+int synthesis_level_tiles(int N, int d, bool wide);
+// whether a launch over these images takes the 256-column workgroups
+bool synthesis_wide(const BatchImage* imgs, int count, int d);
 int analysis_level_tiles(int N, int d);
 // synthesis of level `lev` (thresholded input when thr, else plain W^T); final_out:
 // level 1 writes f, else u
 hipError_t launch_synthesis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
-                                    int lev, int d, int final_out, hipStream_t s, int thr = 1);
+                                    int lev, int d, bool wide, int final_out, hipStream_t s, int thr = 1);
 // z += W w, level `lev`
 hipError_t launch_analysis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
                                    int lev, int d, hipStream_t s);

@@ -64,6 +64,7 @@ struct mlba_unrolled_s {
     std::vector<void*> allocs;
     int* maps = nullptr;
     Map tap_a, tap_at, conv_a, conv_at, pre[3], syn[5], ana[5], adj[5], corr, fill;
+    bool syn_wide[5] = {};  // of syn
     double* dblock = nullptr;  // running partials (doubles), zeroed per backward
     size_t dcount = 0;
     float* eblock = nullptr;   // eacc of every image, zeroed per backward
@@ -139,7 +140,7 @@ int seg_len(const mlba_unrolled_s* U, int j) { return std::min(U->ce, U->iters -
 int enqueue_step(const mlba_unrolled_s* U, const BatchImage* T, hipStream_t s) {
     for (int lev = U->levels; lev >= 1; --lev) {
         const Map& m = U->syn[lev];
-        HIPCHK(launch_synthesis_batched(T, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 0, s));
+        HIPCHK(launch_synthesis_batched(T, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), U->syn_wide[lev], 0, s));
     }
     HIPCHK(launch_tapconv_batched(T, U->tap_a.bmap, U->tap_a.bfirst, U->tap_a.nblocks, 1, U->p, 1, nullptr, s));
     for (int pass = 0; pass < 3; ++pass)
@@ -273,7 +274,9 @@ int mlba_unrolled_create(mlba_unrolled_t* out, int count, const mlba_plan_t* pla
         add(U->pre[pass]);
     }
     for (int lev = 1; lev <= U->levels; ++lev) {
-        for (int i = 0; i < count; ++i) t[i] = synthesis_level_tiles(U->base[i].N, 1 << (lev - 1));
+        U->syn_wide[lev] = synthesis_wide(U->base.data(), count, 1 << (lev - 1));
+        for (int i = 0; i < count; ++i)
+            t[i] = synthesis_level_tiles(U->base[i].N, 1 << (lev - 1), U->syn_wide[lev]);
         add(U->syn[lev]);
         for (int i = 0; i < count; ++i) t[i] = analysis_level_tiles(U->base[i].N, 1 << (lev - 1));
         add(U->ana[lev]);
@@ -380,7 +383,8 @@ int mlba_unrolled_forward(mlba_unrolled_t U, const float* const* g, double alpha
         for (int k = 0; k < seg_len(U, j); ++k) STCHK(enqueue_step(U, table(U, k == 0 ? t_first[j] : t_rest[j]), s));
     for (int lev = U->levels; lev >= 1; --lev) {
         const Map& m = U->syn[lev];
-        HIPCHK(launch_synthesis_batched(table(U, t_out), m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 1, s));
+        HIPCHK(launch_synthesis_batched(table(U, t_out), m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1),
+                                        U->syn_wide[lev], 1, s));
     }
     return note_unrolled(U, s);
 }
@@ -454,7 +458,8 @@ int mlba_unrolled_backward(mlba_unrolled_t U, const float* const* g, double alph
             const BatchImage* T = table(U, t_adj[j][k]);
             for (int lev = U->levels; lev >= 1; --lev) {
                 const Map& m = U->syn[lev];
-                HIPCHK(launch_synthesis_batched(T, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), 0, s, 0));
+                HIPCHK(launch_synthesis_batched(T, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1), U->syn_wide[lev], 0, s,
+                                                0));
             }
             HIPCHK(launch_conv_batched(T, U->conv_a.bmap, U->conv_a.bfirst, U->conv_a.nblocks, 1, U->p, nullptr, s));
             for (int pass = 0; pass < 3; ++pass)
