@@ -41,7 +41,7 @@ struct mlba_batch_s {
     int* maps = nullptr;  // one device buffer holding every map
     size_t maps_cap = 0;  // its size in ints: the largest over every tile choice
     Map conv_a, conv_at, tap_a, tap_at, fold, fill, pre[3], syn[5], ana[5], low[5], shr[5], fill_om;
-    bool syn_wide[5] = {};  // of syn
+    bool syn_wide[5] = {}, shr_wide[5] = {};  // of syn, shr
     // tile choices (set by mlba_batch_autotune)
     int conv_ry[2] = {1, 1};          // output rows per thread of the A and A^T launches
     int rows_want = 0, cols_want = 0;  // transform batching caps (0: built-in choice per size)
@@ -148,7 +148,9 @@ int configure(mlba_batch_s* B, hipStream_t s, bool dry_run = false, size_t* ints
         add(B->ana[lev], t);
         for (int i = 0; i < count; ++i) t[i] = lev < B->levels ? lowpass_level_tiles(B->host[i].N) : 0;
         add(B->low[lev], t);
-        for (int i = 0; i < count; ++i) t[i] = shrink_level_tiles(B->host[i].N, 1 << (lev - 1));
+        B->shr_wide[lev] = shrink_wide(B->host.data(), count, 1 << (lev - 1));
+        for (int i = 0; i < count; ++i)
+            t[i] = shrink_level_tiles(B->host[i].N, 1 << (lev - 1), B->shr_wide[lev]);
         add(B->shr[lev], t);
     }
     if (dry_run) {
@@ -182,7 +184,7 @@ int enqueue_shrink_synthesis(mlba_batch_s* B, int final_out, hipStream_t s) {
     for (int lev = B->levels; lev >= 1; --lev) {
         const Map& m = B->shr[lev];
         HIPCHK(launch_shrink_synthesis_batched(I, m.bmap, m.bfirst, m.nblocks, lev, 1 << (lev - 1),
-                                               lev == B->levels ? 1 : 0, final_out, s));
+                                               B->shr_wide[lev], lev == B->levels ? 1 : 0, final_out, s));
     }
     return MLBA_OK;
 }

@@ -307,11 +307,13 @@ hipError_t launch_lowpass_two_levels(const float* v, int N, float* low1, float* 
 // low_{lev-1}, dilation d = 2^(lev-1)) and the shrink-synthesis of level lev
 // (final_out: level 1 writes f instead of u), over the tiles of all images
 int lowpass_level_tiles(int N);
-int shrink_level_tiles(int N, int d);
+int shrink_level_tiles(int N, int d, bool wide);
+// whether a launch over these images takes the 256-column workgroups
+bool shrink_wide(const BatchImage* imgs, int count, int d);
 hipError_t launch_lowpass_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int lev,
                                   int d, hipStream_t s);
 hipError_t launch_shrink_synthesis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
-                                           int lev, int d, int top, int final_out, hipStream_t s);
+                                           int lev, int d, bool wide, int top, int final_out, hipStream_t s);
 hipError_t launch_shrink_synthesis_level(const float* low, const float* s_in, int N, int d, float* out,
                                          LevelMu mu, float delta, hipStream_t s);
 // batched framelet levels (all images share `levels`); tiles per image:

@@ -112,16 +112,16 @@ hipError_t launch_lowpass_two_levels(const float* v, int N, float* low1, float* 
 // eight bands of the level are computed from low, thresholded and transposed;
 // the (0,0) input is the thresholded low-pass (s_in == null: top level) or
 // s_in, the output of the level above.  Same workgroup geometry as
-// synthesis_tile: one thread per column of an FR_TY-row strip, 256 - 2D
-// output columns per workgroup.
-template <int D, int TY>
+// synthesis_tile: one thread per column of an FR_TY-row strip, W - 2D output
+// columns per workgroup.
+template <int D, int TY, int W>
 struct SsTile {
-    static constexpr int IW = kBlock - 2 * D;  // output columns per workgroup
+    static constexpr int IW = W - 2 * D;       // output columns per workgroup
     static constexpr int HR = TY + 4 * D;      // low-pass rows: y0-2D .. y0+TY+2D-1
     static constexpr int BR = TY + 2 * D;      // band rows: y0-D .. y0+TY+D-1
-    static constexpr int LW = kBlock + 2 * D;  // low-pass columns: x0-2D .. x0+kBlock-1
+    static constexpr int LW = W + 2 * D;       // low-pass columns: x0-2D .. x0+W-1
     static constexpr int LOW_FLOATS = HR * LW;
-    static constexpr int YS_FLOATS = 2 * TY * kBlock;
+    static constexpr int YS_FLOATS = 2 * TY * W;
     static constexpr int LDS_FLOATS = LOW_FLOATS > YS_FLOATS ? LOW_FLOATS : YS_FLOATS;
 };
 
@@ -146,11 +146,11 @@ struct SsTile {
 // Per band (i, j): the threshold of the unnormalised coefficient and its
 // synthesis weight (SsCoef, computed on the host by ss_coef).
 
-template <int D, int TY, bool SIN>
+template <int D, int TY, bool SIN, int W>
 __device__ __forceinline__ void shrink_synthesis_tile(const float* __restrict__ low, const float* __restrict__ s_in,
                                                       int N, float* __restrict__ out, const SsCoef& cf, int bx,
                                                       int by, float* lds) {
-    using G = SsTile<D, TY>;
+    using G = SsTile<D, TY, W>;
     constexpr int HR = G::HR, BR = G::BR, LW = G::LW;
     const int x0 = bx * G::IW;
     const int y0 = by * TY;
@@ -161,10 +161,10 @@ __device__ __forceinline__ void shrink_synthesis_tile(const float* __restrict__ 
     size_t rowo[HR];
 #pragma unroll
     for (int q = 0; q < HR; ++q) rowo[q] = (size_t)reflect_index(y0 - 2 * D + q, N) * N;
-    // tile columns 0 .. kBlock-1: one per thread; the 2D columns beyond them
+    // tile columns 0 .. W-1: one per thread; the 2D columns beyond them
     // (HR x 2D values) spread over the threads, loaded in the same batch
     constexpr int HALO = HR * 2 * D;
-    constexpr int HPT = (HALO + kBlock - 1) / kBlock;
+    constexpr int HPT = (HALO + W - 1) / W;
     float v[HR], hv[HPT];
     int hslot[HPT];
     {
@@ -173,10 +173,10 @@ __device__ __forceinline__ void shrink_synthesis_tile(const float* __restrict__ 
         for (int q = 0; q < HR; ++q) v[q] = low[rowo[q] + col];
 #pragma unroll
         for (int h = 0; h < HPT; ++h) {
-            const int e = h * kBlock + c;
+            const int e = h * W + c;
             hslot[h] = -1;
-            if (HALO % kBlock == 0 || e < HALO) {
-                const int q = e / (2 * D), k = kBlock + e % (2 * D);
+            if (HALO % W == 0 || e < HALO) {
+                const int q = e / (2 * D), k = W + e % (2 * D);
                 hslot[h] = q * LW + k;
                 hv[h] = low[(size_t)reflect_index(y0 - 2 * D + q, N) * N + reflect_index(x0 - 2 * D + k, N)];
             }
@@ -246,25 +246,25 @@ __device__ __forceinline__ void shrink_synthesis_tile(const float* __restrict__ 
         }
     }
     __syncthreads();  // the low-pass tile is no longer read
-    float* ys = lds;  // [2][TY][kBlock]: the terms read from x + d, from x - d
+    float* ys = lds;  // [2][TY][W]: the terms read from x + d, from x - d
     float mid[TY];
 #pragma unroll
     for (int r = 0; r < TY; ++r) {
         const float dlt = acc[0][r] - acc[2][r];
-        ys[r * kBlock + c] = dlt + acc[1][r];
-        ys[(TY + r) * kBlock + c] = dlt - acc[1][r];
+        ys[r * W + c] = dlt + acc[1][r];
+        ys[(TY + r) * W + c] = dlt - acc[1][r];
         mid[r] = acc[0][r] + acc[2][r];
     }
     __syncthreads();
 
-    if (c < D || c >= kBlock - D) return;
+    if (c < D || c >= W - D) return;
     const int x = x0 + c - D;
     if (x >= N) return;
 #pragma unroll
     for (int r = 0; r < TY; ++r) {
         const int y = y0 + r;
         if (y >= N) break;
-        out[(size_t)y * N + x] = fmaf(2.0f, mid[r], ys[r * kBlock + c - D] + ys[(TY + r) * kBlock + c + D]);
+        out[(size_t)y * N + x] = fmaf(2.0f, mid[r], ys[r * W + c - D] + ys[(TY + r) * W + c + D]);
     }
 }
 
@@ -272,14 +272,42 @@ __device__ __forceinline__ void shrink_synthesis_tile(const float* __restrict__ 
 template <int D>
 constexpr int ss_rows() { return 8; }
 
-template <int D, bool SIN>
-__global__ __launch_bounds__(kBlock) void shrink_synthesis_kernel(const float* __restrict__ low,
+// Columns to a workgroup: the kernel is bound by the vector units on images that
+// fill the chip, so the tiling with fewer threads takes it (equal: one wave,
+// whose barriers are free).  1536 x 1536, dilation 1: 1.12 times the threads with
+// 256 columns, 10.5 -> 10.0 us; 2048 x 2048, dilation 2 (1.03): 17.1 -> 16.6;
+// dilation 8, 3000 x 3000 (0.83): 87 us with 256 columns against 101.  32 images
+// of 128 to 1024: 36.2 -> 32.5 and 30.3 -> 27.7 us a level.
+constexpr int SS_WAVE = 64;
+
+static int ss_columns(int N, int d, bool wide) {  // workgroups of a strip
+    const int iw = (wide ? kBlock : SS_WAVE) - 2 * d;
+    return (N + iw - 1) / iw;
+}
+
+int shrink_level_tiles(int N, int d, bool wide) { return ss_columns(N, d, wide) * ((N + 8 - 1) / 8); }
+
+static double ss_threads(int N, int d, bool wide) {
+    return (double)shrink_level_tiles(N, d, wide) * (wide ? kBlock : SS_WAVE);
+}
+
+bool shrink_wide(const BatchImage* imgs, int count, int d) {
+    double wide = 0.0, wave = 0.0;
+    for (int i = 0; i < count; ++i) {
+        wide += ss_threads(imgs[i].N, d, true);
+        wave += ss_threads(imgs[i].N, d, false);
+    }
+    return wide < wave;
+}
+
+template <int D, bool SIN, int W>
+__global__ __launch_bounds__(W) void shrink_synthesis_kernel(const float* __restrict__ low,
                                                                   const float* __restrict__ s_in, int N,
                                                                   float* __restrict__ out, SsCoef cf) {
-    __shared__ float lds[SsTile<D, ss_rows<D>()>::LDS_FLOATS];
+    __shared__ float lds[SsTile<D, ss_rows<D>(), W>::LDS_FLOATS];
     int bx, by;
     xcd_tile(&bx, &by);  // each XCD takes a band of strips: the row halos stay in its L2
-    shrink_synthesis_tile<D, ss_rows<D>(), SIN>(low, s_in, N, out, cf, bx, by, lds);
+    shrink_synthesis_tile<D, ss_rows<D>(), SIN, W>(low, s_in, N, out, cf, bx, by, lds);
 }
 
 hipError_t launch_lowpass_level(const float* v, int N, int d, float* out, hipStream_t s) {
@@ -308,17 +336,15 @@ SsCoef ss_coef(const LevelMu& mu, float delta, bool from_above) {
     return cf;
 }
 
-template <int D>
+template <int D, int W>
 static hipError_t launch_ss(const float* low, const float* s_in, int N, float* out, LevelMu mu, float delta,
                             hipStream_t s) {
-    constexpr int IW = kBlock - 2 * D;
+    constexpr int IW = W - 2 * D;
     constexpr int TY = ss_rows<D>();
     const SsCoef cf = ss_coef(mu, delta, s_in != nullptr);
     dim3 grid((N + IW - 1) / IW, (N + TY - 1) / TY);
-    if (s_in)
-        hipLaunchKernelGGL((shrink_synthesis_kernel<D, true>), grid, dim3(kBlock), 0, s, low, s_in, N, out, cf);
-    else
-        hipLaunchKernelGGL((shrink_synthesis_kernel<D, false>), grid, dim3(kBlock), 0, s, low, s_in, N, out, cf);
+    if (s_in) hipLaunchKernelGGL((shrink_synthesis_kernel<D, true, W>), grid, dim3(W), 0, s, low, s_in, N, out, cf);
+    else hipLaunchKernelGGL((shrink_synthesis_kernel<D, false, W>), grid, dim3(W), 0, s, low, s_in, N, out, cf);
     return hipGetLastError();
 }
 
@@ -328,11 +354,6 @@ static hipError_t launch_ss(const float* low, const float* s_in, int N, float* o
 // buffers, so that every image gets exactly its own plan's arithmetic.
 
 int lowpass_level_tiles(int N) { return ((N + kBlock - 1) / kBlock) * ((N + AN_TY - 1) / AN_TY); }
-
-int shrink_level_tiles(int N, int d) {
-    const int iw = kBlock - 2 * d;
-    return ((N + iw - 1) / iw) * ((N + 8 - 1) / 8);
-}
 
 // low_lev = (b0 x b0) low_{lev-1}, low_0 = omega (the state z)
 template <int D>
@@ -365,58 +386,57 @@ hipError_t launch_lowpass_batched(const BatchImage* imgs, const int* bmap, const
 // the bands of low_{lev-1} (omega at level 1), the level above's output
 // (tmp[(lev + 1) & 1]) below the top, the output to tmp[lev & 1], or at level 1
 // to u (f for the final image).
-template <int D, bool SIN>
-__global__ __launch_bounds__(kBlock) void shrink_synthesis_batched_kernel(const BatchImage* __restrict__ imgs,
+template <int D, bool SIN, int W>
+__global__ __launch_bounds__(W) void shrink_synthesis_batched_kernel(const BatchImage* __restrict__ imgs,
                                                                           const int* __restrict__ bmap,
                                                                           const int* __restrict__ bfirst, int lev,
                                                                           int final_out) {
     constexpr int TY = ss_rows<D>();
-    __shared__ float lds[SsTile<D, TY>::LDS_FLOATS];
+    __shared__ float lds[SsTile<D, TY, W>::LDS_FLOATS];
     const int xb = xcd_block(blockIdx.x, gridDim.x);
     const int im = bmap[xb];
     const BatchImage& I = imgs[im];
     const float* low = lev == 1 ? I.zin : I.lows[lev - 2];
     const float* s_in = SIN ? (((lev + 1) & 1) ? I.tmp1 : I.tmp0) : nullptr;
     float* out = lev == 1 ? (final_out ? I.f : I.u) : ((lev & 1) ? I.tmp1 : I.tmp0);
-    const int gx = (I.N + SsTile<D, TY>::IW - 1) / SsTile<D, TY>::IW;
+    const int gx = (I.N + SsTile<D, TY, W>::IW - 1) / SsTile<D, TY, W>::IW;
     const int local = xb - bfirst[im];
     const int by = local / gx;
-    shrink_synthesis_tile<D, TY, SIN>(low, s_in, I.N, out, I.ss[lev - 1], local - by * gx, by, lds);
+    shrink_synthesis_tile<D, TY, SIN, W>(low, s_in, I.N, out, I.ss[lev - 1], local - by * gx, by, lds);
 }
 
-template <int D>
+template <int D, int W>
 static hipError_t launch_ssb(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int lev,
                              int top, int final_out, hipStream_t s) {
     if (top)
-        hipLaunchKernelGGL((shrink_synthesis_batched_kernel<D, false>), dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap,
+        hipLaunchKernelGGL((shrink_synthesis_batched_kernel<D, false, W>), dim3(nblocks), dim3(W), 0, s, imgs, bmap,
                            bfirst, lev, final_out);
     else
-        hipLaunchKernelGGL((shrink_synthesis_batched_kernel<D, true>), dim3(nblocks), dim3(kBlock), 0, s, imgs, bmap,
+        hipLaunchKernelGGL((shrink_synthesis_batched_kernel<D, true, W>), dim3(nblocks), dim3(W), 0, s, imgs, bmap,
                            bfirst, lev, final_out);
     return hipGetLastError();
 }
 
-hipError_t launch_shrink_synthesis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
-                                           int lev, int d, int top, int final_out, hipStream_t s) {
-    if (nblocks <= 0) return hipSuccess;
-    switch (d) {
-        case 1: return launch_ssb<1>(imgs, bmap, bfirst, nblocks, lev, top, final_out, s);
-        case 2: return launch_ssb<2>(imgs, bmap, bfirst, nblocks, lev, top, final_out, s);
-        case 4: return launch_ssb<4>(imgs, bmap, bfirst, nblocks, lev, top, final_out, s);
-        case 8: return launch_ssb<8>(imgs, bmap, bfirst, nblocks, lev, top, final_out, s);
-        default: return hipErrorInvalidValue;
+#define MLBA_SS_LAUNCH(WIDE, F, ...)                                                       \
+    switch (d) {                                                                           \
+        case 1: return WIDE ? F<1, kBlock>(__VA_ARGS__) : F<1, SS_WAVE>(__VA_ARGS__);      \
+        case 2: return WIDE ? F<2, kBlock>(__VA_ARGS__) : F<2, SS_WAVE>(__VA_ARGS__);      \
+        case 4: return WIDE ? F<4, kBlock>(__VA_ARGS__) : F<4, SS_WAVE>(__VA_ARGS__);      \
+        case 8: return WIDE ? F<8, kBlock>(__VA_ARGS__) : F<8, SS_WAVE>(__VA_ARGS__);      \
+        default: return hipErrorInvalidValue;                                              \
     }
+
+hipError_t launch_shrink_synthesis_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
+                                           int lev, int d, bool wide, int top, int final_out, hipStream_t s) {
+    if (nblocks <= 0) return hipSuccess;
+    MLBA_SS_LAUNCH(wide, launch_ssb, imgs, bmap, bfirst, nblocks, lev, top, final_out, s)
 }
 
 hipError_t launch_shrink_synthesis_level(const float* low, const float* s_in, int N, int d, float* out,
                                          LevelMu mu, float delta, hipStream_t s) {
-    switch (d) {
-        case 1: return launch_ss<1>(low, s_in, N, out, mu, delta, s);
-        case 2: return launch_ss<2>(low, s_in, N, out, mu, delta, s);
-        case 4: return launch_ss<4>(low, s_in, N, out, mu, delta, s);
-        case 8: return launch_ss<8>(low, s_in, N, out, mu, delta, s);
-        default: return hipErrorInvalidValue;
-    }
+    const bool wide = ss_threads(N, d, true) < ss_threads(N, d, false);
+    MLBA_SS_LAUNCH(wide, launch_ss, low, s_in, N, out, mu, delta, s)
 }
+#undef MLBA_SS_LAUNCH
 
 }  // namespace mlba
