@@ -9,6 +9,14 @@
 // table entries of every stage are loaded with the data, the first stage takes
 // its inputs from registers and the last leaves its outputs there.  The radices
 // and their order are the run-time plan's, so the values are too, bit for bit.
+//
+// Forward rows / columns / inverse rows, on the run-time plan -> here, us:
+//   64 x 64 BCCB       5.0 / 10.2 / 4.2  -> 2.8 / 3.7 / 2.7
+//   512 x 512 BCCB     5.7 / 13.3 / 5.7  -> 3.2 / 4.7 / 3.8
+//   512 x 512 DCT      6.4 / 18.3 / 7.3  -> 4.6 / 5.5 / 4.7
+//   1536 x 1536 DCT    15.4 / 25.5 / 20.1 -> 11.8 / 15.3 / 14.7
+// Below 64 a sequence leaves threads without a butterfly; above 1536 one fills a
+// workgroup, which the compiled 2048 and 2304 transforms serve.
 #pragma once
 
 #include "fft_core.hpp"

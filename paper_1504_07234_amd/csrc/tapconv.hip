@@ -10,7 +10,10 @@
 //     moves the gradient of the observations by 6e-5 of its size at 16 x 256 x
 //     256, p = 15, 30 iterations).
 // The implicit state, A^T and the norm estimate use the matrix cores
-// (conv.hip), whose sums are more accurate and 1.3 to 2.9 times as fast.
+// (conv.hip), whose sums are more accurate and at 2048 x 2048 take 21 / 33 / 38 us
+// (p = 5 / 15 / 25) where these take 22 / 43 / 92; 1024 x 1024, p = 49: 47 and 191.
+// Bound by the vector units, 0.78 of their rate at p = 31 (8.1 GFLOP in 131 us at
+// 2048 x 2048), and on small images by the latency of staging the window.
 //
 // One workgroup computes a tile of 64 output columns; the input window is
 // staged once in LDS under the requested boundary extension.  Every thread owns
