@@ -193,7 +193,7 @@ int mlba_version(void);
  * n even, n >= 8) or L = 2(n - 1) (MLBA_PRECOND_AR, which also needs
  * MLBA_BC_ANTIREFLECT; n >= 4).  L = 2^a 3^b 5^c runs as mixed-radix
  * Stockham passes up to L = 2048; any other L runs in Bluestein's chirp
- * form over the smallest power of two m >= 2L - 1, which must be at
+ * form over a length m = 2^a 3^b 5^c >= 2L - 1, which must be at
  * most 2048 (L <= 1024; e.g. the 196 x 196 field of view of section 6's
  * third example: n = 196 for BCCB and DCT, L = 390 for the antireflective
  * transform).  MLBA_EUNSUPPORTED otherwise.  psf: device p x p.

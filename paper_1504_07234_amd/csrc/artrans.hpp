@@ -51,7 +51,7 @@ __device__ __forceinline__ void ar_rows_fwd_body(const float* __restrict__ src, 
         },
         [&](int idx, float2 v) { buf[lds_slot(idx)] = v; });
     __syncthreads();
-    lds_fft_any<-1, NT>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<-1, any_seq(NT)>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     for (int idx = threadIdx.x; idx < G * n; idx += kBlock) {
         const int j = idx / G;
         const int g = idx - j * G;
@@ -115,7 +115,7 @@ __device__ __forceinline__ void ar_cols_filter_body(float* __restrict__ Tr, int 
         lin[2 * q + (threadIdx.x & 1)] = c;
     }
     __syncthreads();
-    lds_fft_any<-1, NT>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<-1, any_seq(NT)>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
 
     // filtered sine coefficients j = 1..N-1, held in registers while the
     // sequence is rebuilt as their odd extension
@@ -157,7 +157,7 @@ __device__ __forceinline__ void ar_cols_filter_body(float* __restrict__ Tr, int 
         buf[lds_slot(q * L + ((threadIdx.x & 1) ? N : 0))] = make_float2(0.0f, 0.0f);
     }
     __syncthreads();
-    lds_fft_any<-1, NT>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<-1, any_seq(NT)>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     for (int idx = threadIdx.x; idx < cp * n; idx += kBlock) {
         const int q = idx / n;
         const int k = idx - q * n;
@@ -200,7 +200,7 @@ __device__ __forceinline__ void ar_rows_inv_body(const float* __restrict__ Tr, i
             buf[lds_slot((idx - k * G) * L + k)] = v;
         });
     __syncthreads();
-    lds_fft_any<-1, NT>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<-1, any_seq(NT)>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     auto emit = [&](int g, int x, float2 c0, float2 cN, float2 prev) {
         const int ya = row0 + 2 * g;
         const float2 X = buf[lds_slot(g * L + x)];

@@ -316,7 +316,7 @@ __device__ __forceinline__ void dct_rows_fwd_body(const float* __restrict__ src,
             buf[lds_slot(g * n + dct_perm(idx - g * n, n))] = v;
         });
     __syncthreads();
-    lds_fft_any<-1, NT>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<-1, any_seq(NT)>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     for (int idx = threadIdx.x; idx < G * n; idx += kBlock) {
         const int k = idx / G;
         const int g = idx - k * G;
@@ -382,7 +382,7 @@ __device__ __forceinline__ void dct_cols_filter_body(float* __restrict__ Tr, int
                 buf[lds_slot(q * n + dct_perm(idx - q * n, n))] = v;
             });
         __syncthreads();
-        lds_fft_any<-1, NT>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+        lds_fft_any<-1, any_seq(NT)>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
 #pragma unroll
         for (int i = 0; i < FFT_EPT; ++i) {
             const int idx = threadIdx.x + i * kBlock;
@@ -452,7 +452,7 @@ __device__ __forceinline__ void dct_cols_filter_body(float* __restrict__ Tr, int
         if (idx < total) buf[lds_slot(idx)] = keep[i];
     }
     __syncthreads();
-    lds_fft_any<1, NT>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<1, any_seq(NT)>(buf, fd, cp, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     for (int idx = threadIdx.x; idx < total; idx += kBlock) {
         const int q = idx / n;
         const int l = idx - q * n;
@@ -509,7 +509,7 @@ __device__ __forceinline__ void dct_rows_inv_body(const float* __restrict__ Tr, 
         if (idx < total) buf[lds_slot(idx)] = keep[i];
     }
     __syncthreads();
-    lds_fft_any<1, NT>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
+    lds_fft_any<1, any_seq(NT)>(buf, fd, G, seq_shift, tw, NT > 0 ? twp.w : nullptr);
     for (int idx = threadIdx.x; idx < total; idx += kBlock) {
         const int g = idx / n;
         const int x = idx - g * n;

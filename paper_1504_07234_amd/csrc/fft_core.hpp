@@ -21,8 +21,9 @@ constexpr int kFixedM2 = 1152;  // the FFT-blur grid of ~1K images (unknowns of 
 constexpr int FFT_MAX_ELEMS = FFT_EPT * kBlock;  // complex values per workgroup (16 KB of LDS)
 
 // n = 2^a 3^b 5^c: a Stockham plan of n itself; otherwise the Bluestein form
-// over bluestein_len(n), the smallest power of two >= 2n - 1 (and 64), whose
-// transforms are compiled (fft_seq.hpp).
+// over a length m >= 2n - 1 (fft_desc): bluestein_len(n), the smallest power of two
+// (and 64), whose transforms are compiled (fft_seq.hpp), or at most that, the
+// smallest 2^a 3^b 5^c.
 __host__ __device__ constexpr bool smooth235(int n) {
     if (n < 1) return false;
     while (n % 2 == 0) n /= 2;
@@ -382,10 +383,60 @@ __device__ __forceinline__ void lds_stockham(float2* buf, int len, const FftDesc
 }
 
 // Length-n DFT of the one sequence in buf[0, n) by Bluestein's identity
-// (fft_seq.hpp); buf holds m slots, every thread of the workgroup takes part
-// (m <= FFT_MAX_ELEMS).
+// jk = (j^2 + k^2 - (k - j)^2) / 2:
+//   X_k = c_k sum_j (x_j c_j) conj(c_{k-j}),  c_k = exp(-i pi k^2 / n),
+// the sum a circular convolution of length m >= 2n - 1 done with two m-point
+// transforms and the stored spectrum of conj(c) (scaled by 1/m).  The inverse
+// direction is conj(DFT(conj x)).  buf holds m slots; every thread of the
+// workgroup takes part (m <= FFT_MAX_ELEMS).  On the run-time plan of m =
+// 2^a 3^b 5^c.
+template <int DIR, int EPT = FFT_EPT>
+__device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __restrict__ tw) {
+    constexpr int KE = FFT_MAX_ELEMS / kBlock;
+    const int n = fd.n, m = fd.m;
+    const float2* __restrict__ chirp = tw + m;
+    const float2* __restrict__ bspec = tw + m + n;
+    float2 a[KE];
+#pragma unroll
+    for (int j = 0; j < KE; ++j) {
+        const int k = (int)threadIdx.x + j * kBlock;
+        a[j] = make_float2(0.0f, 0.0f);
+        if (k < n) {
+            float2 x = buf[lds_slot(k)];
+            if (DIR > 0) x.y = -x.y;
+            a[j] = cmul(x, chirp[k]);
+        }
+    }
+    __syncthreads();  // every x read before the zero padding overwrites it
+#pragma unroll
+    for (int j = 0; j < KE; ++j) {
+        const int k = (int)threadIdx.x + j * kBlock;
+        if (k < m) buf[lds_slot(k)] = a[j];
+    }
+    __syncthreads();
+    lds_stockham<-1, EPT>(buf, m, fd, 1, 8, tw);
+#pragma unroll
+    for (int j = 0; j < KE; ++j) {
+        const int k = (int)threadIdx.x + j * kBlock;
+        if (k < m) buf[lds_slot(k)] = cmul(buf[lds_slot(k)], bspec[k]);
+    }
+    __syncthreads();
+    lds_stockham<1, EPT>(buf, m, fd, 1, 8, tw);
+#pragma unroll
+    for (int j = 0; j < KE; ++j) {
+        const int k = (int)threadIdx.x + j * kBlock;
+        if (k < n) {
+            float2 v = cmul(buf[lds_slot(k)], chirp[k]);
+            if (DIR > 0) v.y = -v.y;
+            buf[lds_slot(k)] = v;
+        }
+    }
+    __syncthreads();
+}
+
+// On compiled transforms, m a power of two (fft_seq.hpp).
 template <int DIR>
-__device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __restrict__ tw);
+__device__ void lds_bluestein_seq(float2* buf, const FftDesc& fd, const float2* __restrict__ tw);
 
 // run-time 2/3/5-smooth lengths
 template <int DIR, int EPT = FFT_EPT>
@@ -398,6 +449,10 @@ __device__ __forceinline__ void lds_fft(float2* buf, const FftDesc& fd, int nseq
 // Stockham plan only, which keeps the Bluestein code (and its registers) out
 // of the kernels that serve 2/3/5-smooth lengths.
 constexpr int kAnyLen = -1;
+// the same with the compiled Bluestein form (in one kernel with the run-time form
+// its registers cost both of them a third of their speed)
+constexpr int kAnySeq = -2;
+__host__ __device__ constexpr int any_seq(int nt) { return nt == kAnyLen ? kAnySeq : nt; }
 
 // ---- fixed-size transforms ------------------------------------------------
 // The same Stockham stages with the length known at compile time and one
@@ -674,15 +729,18 @@ __device__ __forceinline__ void fixed_conv(float2* buf, const float2* __restrict
 
 // NT > 0: the fixed transform of length NT (one sequence per workgroup),
 // with the twiddles of fixed_tw_load in `pre` when given; NT == 0: the
-// run-time plan fd over nseq sequences; NT == kAnyLen: that, or the
-// Bluestein form when fd.m > 0.
+// run-time plan fd over nseq sequences; NT == kAnyLen (kAnySeq): that, or the
+// Bluestein form (the compiled one) when fd.m > 0.
 template <int DIR, int NT, int EPT = FFT_EPT>
 __device__ __forceinline__ void lds_fft_any(float2* buf, const FftDesc& fd, int nseq, int seq_shift,
                                             const float2* __restrict__ tw, const float2* pre = nullptr) {
     if constexpr (NT > 0) {
         lds_fft_fixed<DIR, NT>(buf, tw, pre);
     } else if constexpr (NT == kAnyLen) {
-        if (fd.m > 0) lds_bluestein<DIR>(buf, fd, tw);  // one sequence per workgroup
+        if (fd.m > 0) lds_bluestein<DIR, EPT>(buf, fd, tw);  // one sequence per workgroup
+        else lds_fft<DIR, EPT>(buf, fd, nseq, seq_shift, tw);
+    } else if constexpr (NT == kAnySeq) {
+        if (fd.m > 0) lds_bluestein_seq<DIR>(buf, fd, tw);  // one sequence per workgroup
         else lds_fft<DIR, EPT>(buf, fd, nseq, seq_shift, tw);
     } else {
         lds_fft<DIR, EPT>(buf, fd, nseq, seq_shift, tw);

@@ -215,8 +215,8 @@ __device__ __forceinline__ void seq_sync_all() {
 // (the same values to the same slots) to keep the barriers.  A pass is bound by
 // the latency of its chain of stages: on the run-time plan of the smallest
 // 2^a 3^b 5^c >= 2n - 1 each of them had a table read, run-time strides and two
-// barriers.  P at n = 66 / 226 / 514 / 1022, BCCB: 41 / 43 / 65 / 67 -> 19 / 21 /
-// 33 / 40 us; antireflective n = 196 / 500: 50 / 86 -> 30 / 35 us.  M is a power of
+// barriers.  P at n = 66 / 226 / 514 / 1022, DCT: 42 / 45 / 69 / 74 -> 21 / 23 /
+// 37 / 47 us; antireflective n = 196 / 500: 50 / 86 -> 30 / 35 us.  M is a power of
 // two also where 3 2^a or 5-smooth is shorter (n = 66: m = 135 -> 256, 514:
 // 1080 -> 2048): the longer compiled chain is still half the run-time plan's.
 template <int DIR, int M>
@@ -263,7 +263,7 @@ __device__ __forceinline__ void seq_bluestein(float2* buf, int n, const float2* 
 }
 
 template <int DIR>
-__device__ void lds_bluestein(float2* buf, const FftDesc& fd, const float2* __restrict__ tw) {
+__device__ void lds_bluestein_seq(float2* buf, const FftDesc& fd, const float2* __restrict__ tw) {
     switch (fd.m) {
         case 64: return seq_bluestein<DIR, 64>(buf, fd.n, tw);
         case 128: return seq_bluestein<DIR, 128>(buf, fd.n, tw);

@@ -39,13 +39,20 @@ bool factor_235(int n, int* a, int* b, int* c) {
 // 9 stages, as in the compiled plans, measured 3-6 % slower here: with
 // several short sequences per workgroup half the threads idle in them and the
 // larger butterflies cost occupancy.)
-// Any other n takes the Bluestein form over m = bluestein_len(n) (stages of m).
-FftDesc fft_desc(int n) {
+// Any other n takes the Bluestein form (stages of m).  Its length m: the compiled
+// bluestein_len(n) for the DCT and the antireflective transform (twice as fast);
+// for the BCCB matrix the smallest 2^a 3^b 5^c >= 2n - 1, since the unrolled form
+// differentiates its iterations and the gradient depends on the active sets {|z| >
+// mu}: another rounding of P moves it by 2e-5 of its size.
+FftDesc fft_desc(int n, bool bccb) {
     FftDesc d{};
     d.n = n;
     int a = 0, b = 0, c = 0;
     if (!factor_235(n, &a, &b, &c)) {
         d.m = bluestein_len(n);
+        if (bccb)
+            for (d.m = 2 * n - 1; !factor_235(d.m, &a, &b, &c);) ++d.m;
+        a = b = c = 0;
         factor_235(d.m, &a, &b, &c);
     }
     for (; a >= 3; a -= 3) d.radix[d.nst++] = 8;
@@ -102,7 +109,7 @@ std::vector<float2> fft_table(const FftDesc& d) {
 
 }  // namespace
 
-FftDesc mlba_internal_fft_desc(int n) { return fft_desc(n); }
+FftDesc mlba_internal_fft_desc(int n) { return fft_desc(n, true); }
 
 namespace {
 
@@ -930,7 +937,7 @@ int mlba_plan_create(mlba_plan_t* plan, int n, int p, int bc, int precond, int l
 
     if (precond != MLBA_PRECOND_NONE) {
         const int L = precond == MLBA_PRECOND_AR ? 2 * (n - 1) : n;  // transform length
-        P->fd = fft_desc(L);
+        P->fd = fft_desc(L, precond == MLBA_PRECOND_BCCB);
 
         // the cosine table serves the eigenvalues: angles pi q / n (DCT) or
         // pi q / (n - 1) (antireflective transform); BCCB does not read it
@@ -1036,7 +1043,7 @@ int ensure_fftconv(mlba_plan_s* P, hipStream_t s) {
     FftConv c{};
     c.M = M;
     c.ts = M + 16;
-    c.fd = fft_desc(M);
+    c.fd = fft_desc(M, true);
     std::vector<float2> tw(M);
     const double pi = 3.14159265358979323846;
     for (int q = 0; q < M; ++q) {
