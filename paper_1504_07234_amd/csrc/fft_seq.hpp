@@ -196,6 +196,21 @@ struct Seq {
     }
 };
 
+// A sequence inside one wave orders its accesses by itself and may leave the
+// kernel when it has nothing to do; one of several waves stays for the
+// workgroup's barriers.
+template <int N>
+constexpr bool seq_alone() {
+    return seq_threads(N) <= 64;
+}
+
+// Whether sequence k of `count`, G to a workgroup, is one of them.
+template <int COUNT, int G>
+__device__ __forceinline__ bool seq_live(int k) {
+    if constexpr (COUNT % G == 0) return true;
+    else return k < COUNT;
+}
+
 // Workgroup-wide order where a pass touches other sequences' slots.
 template <int N, int THREADS>
 __device__ __forceinline__ void seq_sync_all() {
@@ -330,17 +345,19 @@ __device__ __forceinline__ void seq_cols(float2* __restrict__ T, int ts, const f
     using Q = Seq<N>;
     const int g = threadIdx.x / TH, t = threadIdx.x % TH, k = blk * G + g;
     float2* buf = lds + g * seq_slots(N);
-    if (k >= half) return;  // whole sequences: the others of this wave go on alone (TH <= 64), or none (G = 1)
+    const bool live = seq_live<half, G>(k);
+    if (seq_alone<N>() && !live) return;
     Q q;
     q.load_tw(tw, t);
     float2 v[8], u[Q::BL][Q::RL];
     float sp[Q::BL][Q::RL];
     float2* col = T + (size_t)k * ts;
     const size_t base = (size_t)k * N;  // dense [N/2+1][N] spectrum
-    Q::inputs(t, [&](int r, int y) { v[r] = col[y]; });
-    Q::outputs(t, [&](int i, int r, int y) { sp[i][r] = spec[base + y]; });
+    Q::inputs(t, [&](int r, int y) { v[r] = live ? col[y] : make_float2(0.0f, 0.0f); });
+    Q::outputs(t, [&](int i, int r, int y) { sp[i][r] = live ? spec[base + y] : 1.0f; });
     q.template run<-1>(v, u, buf, t);
     Q::outputs(t, [&](int i, int r, int y) {
+        if (!live) return;
         float2 x = cscale(u[i][r], inv / (sp[i][r] + alpha));
         if (lamc) x = cmul(x, cconj(lamc[base + y]));
         if (sstore) sstore[base + y] = x;  // reverse sweep of unrolled iterations
@@ -361,23 +378,28 @@ __device__ __forceinline__ void seq_cols(float2* __restrict__ T, int ts, const f
         seq_sync<N>();
     }
     q.template run<1>(v, u, buf, t);
-    Q::outputs(t, [&](int i, int r, int y) { col[y] = u[i][r]; });
+    Q::outputs(t, [&](int i, int r, int y) {
+        if (live) col[y] = u[i][r];
+    });
 }
 
 // columns: inverse transform of the real dense spectrum e into T
 template <int N, int THREADS>
 __device__ __forceinline__ void seq_cols_inverse_real(const float* __restrict__ e, float2* __restrict__ T, int ts,
                                                       const float2* __restrict__ tw, int blk, float2* lds) {
-    constexpr int TH = seq_threads(N), G = THREADS / TH;
+    constexpr int TH = seq_threads(N), G = THREADS / TH, half = N / 2 + 1;
     using Q = Seq<N>;
     const int g = threadIdx.x / TH, t = threadIdx.x % TH, k = blk * G + g;
-    if (k >= N / 2 + 1) return;  // as in seq_cols
+    const bool live = seq_live<half, G>(k);
+    if (seq_alone<N>() && !live) return;
     Q q;
     q.load_tw(tw, t);
     float2 v[8], u[Q::BL][Q::RL];
-    Q::inputs(t, [&](int r, int y) { v[r] = make_float2(e[(size_t)k * N + y], 0.0f); });
+    Q::inputs(t, [&](int r, int y) { v[r] = make_float2(live ? e[(size_t)k * N + y] : 0.0f, 0.0f); });
     q.template run<1>(v, u, lds + g * seq_slots(N), t);
-    Q::outputs(t, [&](int i, int r, int y) { T[(size_t)k * ts + y] = u[i][r]; });
+    Q::outputs(t, [&](int i, int r, int y) {
+        if (live) T[(size_t)k * ts + y] = u[i][r];
+    });
 }
 
 // put(i, v): the value v of flat index i of the N x N output
@@ -411,6 +433,7 @@ __device__ __forceinline__ void seq_rows_c2r(const float2* __restrict__ T, int t
         }
     }
     seq_sync_all<N, THREADS>();
+    static_assert(seq_alone<N>() || (N / 2) % G == 0, "a sequence of several waves is live: barriers ahead");
     if (2 * (pair0 + g) >= N) return;
     float2 v[8], u[Q::BL][Q::RL];
     Q::inputs(t, [&](int r, int k) { v[r] = buf[lds_slot(k)]; });
@@ -486,7 +509,8 @@ __device__ __forceinline__ void seq_dct_cols(float* __restrict__ Tr, int ts, con
     using Q = Seq<N>;
     const int g = threadIdx.x / TH, t = threadIdx.x % TH, p = blk * G + g;
     float2* buf = lds + g * seq_slots(N);
-    if (2 * p >= N) return;  // as in seq_cols
+    static_assert(seq_alone<N>() || (N / 2) % G == 0, "a sequence of several waves is live: barriers ahead");
+    if (2 * p >= N) return;
     Q q;
     q.load_tw(tw, t);
     float* r1 = Tr + (size_t)2 * p * ts;
@@ -554,6 +578,7 @@ __device__ __forceinline__ void seq_dct_rows_inv(const float* __restrict__ Tr, i
         if (idx < G * N && 2 * (pair0 + h) < N) lds[h * seq_slots(N) + lds_slot(k)] = in[i];
     }
     seq_sync_all<N, THREADS>();
+    static_assert(seq_alone<N>() || (N / 2) % G == 0, "a sequence of several waves is live: barriers ahead");
     if (2 * (pair0 + g) >= N) return;
     float2 v[8], u[Q::BL][Q::RL];
     Q::inputs(t, [&](int r, int k) {
