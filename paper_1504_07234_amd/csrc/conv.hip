@@ -28,9 +28,15 @@
 // 2048, p = 15 / 25, now 33 / 38 (the relative error 1.2e-7 / 1.8e-7 instead of
 // 2.5e-7 / 4.2e-7).
 //
-// bfloat16 has float32's exponent range, so nothing is scaled; a window with a
-// value that is not finite in bfloat16 takes the plain tap loop, whose
-// infinities and NaN reach exactly the outputs whose taps touch them.
+// bfloat16 has float32's exponent range, so nothing is scaled.  What the split
+// cannot hold takes the plain tap loop:
+//   - a window or a PSF with a value that is not finite in bfloat16 (infinities
+//     and NaN reach exactly the outputs whose taps touch them);
+//   - values so large that the sum of the rounded first parts could overflow
+//     where the blur does not;
+//   - a window or a PSF whose largest value is below 2^-95, where the third parts
+//     leave bfloat16's range (2^-133): at 2^-115 the error was 5.6e-7, in the tap
+//     loop 1.5e-7.  A smaller value beside larger ones loses less than 2^-133.
 //
 // The tile body is a device function shared by the single-image kernels and
 // the batched kernel (one launch covering the tiles of many images); an
@@ -71,8 +77,19 @@ static int conv_tiles_r(int D, int r) {
     return ((D + CONV_TX - 1) / CONV_TX) * ((D + conv_ty(r) - 1) / conv_ty(r));
 }
 
-// PSF rows a = -1 .. p + CONV_AHEAD (zero outside [0, p))
-size_t conv_taps_elems(int p) { return (size_t)(p + 2 + CONV_AHEAD) * CONV_SPLITS * conv_depth(p) * 32; }
+// PSF rows a = -1 .. p + CONV_AHEAD (zero outside [0, p)), then one element for
+// the windows these taps can be multiplied with: the bits of the largest value
+// allowed in one, and whether the taps need the plain loop with any of them
+__host__ __device__ constexpr int conv_taps_range(int p) {
+    return (p + 2 + CONV_AHEAD) * CONV_SPLITS * conv_depth(p) * 32;
+}
+size_t conv_taps_elems(int p) { return (size_t)conv_taps_range(p) + 1; }
+
+constexpr unsigned CONV_LEAST = 0x10000000u;    // 2^-95
+constexpr unsigned CONV_LARGEST = 0x7f7f0000u;  // the largest bfloat16 value
+
+// the bits of |x|: ordered as the values, NaN above infinity
+__device__ __forceinline__ unsigned abs_bits(float x) { return __builtin_bit_cast(unsigned, x) & 0x7fffffffu; }
 
 __device__ __forceinline__ void split3(float x, __bf16* h) {
     h[0] = (__bf16)x;
@@ -96,6 +113,22 @@ __global__ __launch_bounds__(64) void conv_taps_kernel(const float* __restrict__
             for (int i = 0; i < p * p; ++i) sum += (double)h[i];
             *l1 = sum;
         }
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        unsigned top = 0;
+        float sum = 0.0f;
+        for (int i = threadIdx.x; i < p * p; i += 64) {
+            top = max(top, abs_bits(psf[i]));
+            sum += fabsf(psf[i]);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            top = max(top, (unsigned)__shfl_xor((int)top, off, 64));
+            sum += __shfl_xor(sum, off, 64);
+        }
+        const bool plain = top > CONV_LARGEST || (top > 0 && top < CONV_LEAST);
+        const unsigned most = min(CONV_LARGEST, abs_bits(0x1p126f / sum));
+        if (threadIdx.x < 2)
+            (threadIdx.x ? taps1 : taps0)[conv_taps_range(p)] = make_uint4(most, plain ? 1u : 0u, 0u, 0u);
     }
     const int a = (int)blockIdx.x - 1, q = blockIdx.y, flip = threadIdx.x >> 5, l = threadIdx.x & 31;
     bf16x8 f[CONV_SPLITS];
@@ -125,14 +158,14 @@ struct __attribute__((packed, aligned(4))) FloatQuad {
     float v[4];
 };
 
-// Splits four values into the rows of the window; chk collects what is left
-// below the second part, which is NaN unless the value is finite in bfloat16.
+// Splits four values into the rows of the window; top: the largest abs_bits seen.
 template <int C>
-__device__ __forceinline__ void conv_put_split(__bf16* win, const float* v, float* chk) {
+__device__ __forceinline__ void conv_put_split(__bf16* win, const float* v, unsigned* top) {
     unsigned w[CONV_SPLITS][2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         float r0 = v[2 * e], r1 = v[2 * e + 1];
+        *top = max(*top, max(abs_bits(r0), abs_bits(r1)));
 #pragma unroll
         for (int s = 0; s < CONV_SPLITS; ++s) {
             w[s][e] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
@@ -141,7 +174,6 @@ __device__ __forceinline__ void conv_put_split(__bf16* win, const float* v, floa
                 r1 -= __builtin_bit_cast(float, w[s][e] & 0xffff0000u);
             }
         }
-        *chk += r0 + r1;
     }
 #pragma unroll
     for (int s = 0; s < CONV_SPLITS; ++s) *(uint2*)(win + s * C) = make_uint2(w[s][0], w[s][1]);
@@ -185,32 +217,32 @@ __device__ __forceinline__ void conv_fetch(const ConvJob& j, int P, int TY, int 
     }
 }
 
-// Returns whether some value is not finite in bfloat16.  A window that leaves
-// the image under the antireflective extension (up to four sources a value) is
-// read here, row by row.
+// Returns the largest abs_bits of the thread's values.  A window that leaves the
+// image under the antireflective extension (up to four sources a value) is read
+// here, row by row.
 template <int KC, int U>
-__device__ __forceinline__ bool conv_commit(const ConvJob& j, int P, int TY, int oy0, int ox0, float (&v)[U][4],
+__device__ __forceinline__ unsigned conv_commit(const ConvJob& j, int P, int TY, int oy0, int ox0, float (&v)[U][4],
                                             __bf16* win) {
     constexpr int C = conv_cols(KC), LS = conv_row_elems(KC), RS = kBlock / 32;
     const int rows = TY + P - 1;
     const int lx = 4 * ((int)threadIdx.x & 31), ly0 = (int)threadIdx.x >> 5;
     const int S = j.S, y0 = oy0 + j.org, x0 = ox0 + j.org;
-    if (lx >= C) return false;
-    float chk = 0.0f;
+    unsigned top = 0;
+    if (lx >= C) return top;
     if (j.ext == EXT_ANTIREFLECT && !(y0 >= 0 && x0 >= 0 && y0 + rows <= S && x0 + C <= S)) {
 #pragma unroll 1
         for (int ly = ly0; ly < rows; ly += RS) {
             float q[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) q[e] = fetch_antireflect(j.src, S, y0 + ly, x0 + lx + e);
-            conv_put_split<C>(win + ly * LS + lx, q, &chk);
+            conv_put_split<C>(win + ly * LS + lx, q, &top);
         }
-        return chk != chk;
+        return top;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (ly0 + u * RS < rows) conv_put_split<C>(win + (ly0 + u * RS) * LS + lx, v[u], &chk);
-    return chk != chk;
+        if (ly0 + u * RS < rows) conv_put_split<C>(win + (ly0 + u * RS) * LS + lx, v[u], &top);
+    return top;
 }
 
 // dst = g - v (returning v's square sum), dst + v or v
@@ -350,14 +382,22 @@ template <int KC, int R>
 __device__ __forceinline__ double conv_tile(const ConvJob& j, int P, int flip, int oy0, int ox0, __bf16* win) {
     constexpr int PMAX = KC == 1 ? CONV_K1 : CONV_PMAX;
     constexpr int U = (conv_ty(R) + PMAX - 1 + 7) / 8;
-    __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
+    __shared__ int bad, large, some;
+    const uint4 range = j.taps[conv_taps_range(P)];
+    if (threadIdx.x == 0) {
+        bad = range.y;
+        large = some = 0;
+    }
     float v[U][4];
     conv_fetch<KC, U>(j, P, conv_ty(R), oy0, ox0, v);
     __syncthreads();
-    if (conv_commit<KC, U>(j, P, conv_ty(R), oy0, ox0, v, win)) bad = 1;
+    const unsigned top = conv_commit<KC, U>(j, P, conv_ty(R), oy0, ox0, v, win);
+    if (top > range.x) bad = 1;
+    if (top >= CONV_LEAST) large = 1;
+    else if (top > 0) some = 1;
     __syncthreads();
-    return bad ? conv_tile_taps(j, P, flip, conv_ty(R), oy0, ox0) : conv_products<KC, R>(j, P, oy0, ox0, win);
+    return bad || (some && !large) ? conv_tile_taps(j, P, flip, conv_ty(R), oy0, ox0)
+                                   : conv_products<KC, R>(j, P, oy0, ox0, win);
 }
 
 // ---- single-image kernels -----------------------------------------------
