@@ -209,10 +209,15 @@ int mlba_plan_destroy(mlba_plan_t plan);
 /* How the blur A and its transpose (or, antireflective model, its reblur
  * A') are computed:
  * MLBA_BLUR_DIRECT (default): LDS-tiled direct convolution, p^2 taps per
- * output, with the implicit state on the matrix cores, with the explicit state
- * and in mlba_apply_A / mlba_residual in the order of the taps; MLBA_BLUR_FFT: circular convolution on an M x M grid, M >= m =
+ * output.  The calls whose result hangs on the order of that sum keep the
+ * order of the taps: eq. (MLBA2) with the explicit state, mlba_apply_A and
+ * mlba_residual.  The others (the implicit state, Algorithms 2 and 4 with
+ * either state, mlba_apply_At, the norm estimates) run on the matrix cores.
+ * MLBA_BLUR_FFT: circular convolution on an M x M grid, M >= m =
  * n + p - 1, M = 2^a 3^b (section 2.1's FFT evaluation), three passes per
- * product: row transforms, a column pass, inverse row transforms.  For
+ * product: row transforms, a column pass, inverse row transforms.
+ * MLBA_BLUR_FFT_TAPS: the grid for the calls that keep the order of the taps,
+ * the matrix cores for the others.  For
  * p = 5, 9, 17 and 31 the column pass is the p-tap convolution along y with
  * the PSF's rows transformed the same way (the same values as the column
  * transform pair with F(pad H) on every output that does not wrap around;
@@ -222,19 +227,22 @@ int mlba_plan_destroy(mlba_plan_t plan);
  * by the pad's transpose.  With the periodic model and MLBA_PRECOND_BCCB,
  * MLBA_BLUR_FFT also selects for eq. (MLBA2) the spectral residual of
  * Algorithm 4 (A = C there): one 2-D transform pair per iteration.
- * mlba_plan_set_blur: MLBA_BLUR_FFT allocates the grid's workspace and PSF
+ * mlba_plan_set_blur: a mode with the grid allocates its workspace and PSF
  * spectrum on first use (synchronous) and returns MLBA_EUNSUPPORTED when M
- * would exceed 3072.  mlba_plan_autotune:
- * times them on the plan's own scratch buffers (`reps` calls each, HIP events,
- * synchronous), keeps the faster pair, for the calls that keep the order of the
- * taps against that form of the direct blur, writes the mean ms per call to
- * ms_out (host, optional: direct A, direct A^T on the matrix cores, FFT A, FFT
- * A^T; -1 where unavailable) and returns the mode chosen against those (>= 0)
- * or an error. */
-#define MLBA_BLUR_DIRECT 0
-#define MLBA_BLUR_FFT    1
+ * would exceed 3072.  mlba_plan_autotune: times the grid and both forms of the
+ * direct blur on the plan's own scratch buffers (`reps` calls each, HIP
+ * events, synchronous), keeps the fastest for either kind of call,
+ * writes the mean ms per call to ms_out (host, optional:
+ * direct A, direct A^T on the matrix cores, FFT A, FFT A^T; -1 where
+ * unavailable) and returns the mode, which mlba_plan_set_blur takes for another
+ * plan of these sizes, or an error.  mlba_plan_taps_ms: the last autotune's ms of
+ * A and A^T in the order of the taps, to ms_out[2] (-1 before it). */
+#define MLBA_BLUR_DIRECT   0
+#define MLBA_BLUR_FFT      1
+#define MLBA_BLUR_FFT_TAPS 2
 int mlba_plan_set_blur(mlba_plan_t plan, int mode, hipStream_t stream);
 int mlba_plan_autotune(mlba_plan_t plan, int reps, double* ms_out, hipStream_t stream);
+int mlba_plan_taps_ms(mlba_plan_t plan, double* ms_out);
 /* Sizes: observed side n, PSF side p, unknown side N, number of bands. */
 int mlba_plan_dims(mlba_plan_t plan, int* n, int* p, int* N, int* bands);
 /* ||A^T P_alpha A||, the largest eigenvalue of the symmetric positive

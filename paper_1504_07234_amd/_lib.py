@@ -18,7 +18,7 @@ BC_RECT, BC_REFLECT, BC_PERIODIC, BC_ZERO, BC_ANTIREFLECT = 0, 1, 2, 3, 4
 PRECOND_BCCB, PRECOND_DCT, PRECOND_NONE, PRECOND_AR = 0, 1, 2, 3
 ALPHA_CONST, ALPHA_GEOMETRIC, ALPHA_TABLE, ALPHA_NS = 0, 1, 2, 3
 METHOD_MLBA, METHOD_ALG4, METHOD_ALG2 = 0, 1, 2
-BLUR_DIRECT, BLUR_FFT = 0, 1
+BLUR_DIRECT, BLUR_FFT, BLUR_FFT_TAPS = 0, 1, 2
 STATE_EXPLICIT, STATE_IMPLICIT = 0, 1
 
 c_int, c_double, c_size_t, c_void_p = ctypes.c_int, ctypes.c_double, ctypes.c_size_t, ctypes.c_void_p
@@ -58,6 +58,7 @@ SIGNATURES = {
     "mlba_plan_destroy": (c_int, [c_void_p]),
     "mlba_plan_set_blur": (c_int, [c_void_p, c_int, c_void_p]),
     "mlba_plan_autotune": (c_int, [c_void_p, c_int, c_dbl_p, c_void_p]),
+    "mlba_plan_taps_ms": (c_int, [c_void_p, c_dbl_p]),
     "mlba_plan_dims": (c_int, [c_void_p, c_int_p, c_int_p, c_int_p, c_int_p]),
     "mlba_plan_opnorm": (c_int, [c_void_p, c_double, c_int, c_dbl_p, c_void_p]),
     "mlba_apply_A": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p]),

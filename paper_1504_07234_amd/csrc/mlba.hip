@@ -1104,9 +1104,10 @@ int time_ms(F f, int reps, hipStream_t s, double* ms) {
 extern "C" {
 
 int mlba_plan_set_blur(mlba_plan_t P, int mode, hipStream_t s) {
-    if (!P || mode < MLBA_BLUR_DIRECT || mode > MLBA_BLUR_FFT) return MLBA_EINVAL;
-    if (mode == MLBA_BLUR_FFT) STCHK(ensure_fftconv(P, s));
-    P->blur_fft = P->blur_fft_taps = mode == MLBA_BLUR_FFT ? 1 : 0;
+    if (!P || mode < MLBA_BLUR_DIRECT || mode > MLBA_BLUR_FFT_TAPS) return MLBA_EINVAL;
+    if (mode != MLBA_BLUR_DIRECT) STCHK(ensure_fftconv(P, s));
+    P->blur_fft = mode == MLBA_BLUR_FFT ? 1 : 0;
+    P->blur_fft_taps = mode != MLBA_BLUR_DIRECT ? 1 : 0;
     return MLBA_OK;
 }
 
@@ -1132,12 +1133,20 @@ int mlba_plan_autotune(mlba_plan_t P, int reps, double* ms_out, hipStream_t s) {
             return st;
         }
     }
+    // the taps are at most as fast as the matrix cores
     const double fft = have_fft == MLBA_OK ? t[1][0] + t[1][1] : 1e300;
     P->blur_fft = fft < t[0][0] + t[0][1] ? 1 : 0;
-    P->blur_fft_taps = fft < t[2][0] + t[2][1] ? 1 : 0;
+    P->blur_fft_taps = P->blur_fft || fft < t[2][0] + t[2][1] ? 1 : 0;
+    for (int i = 0; i < 2; ++i) P->taps_ms[i] = t[2][i];
     if (ms_out)
         for (int i = 0; i < 4; ++i) ms_out[i] = t[i / 2][i % 2];
-    return P->blur_fft ? MLBA_BLUR_FFT : MLBA_BLUR_DIRECT;
+    return P->blur_fft ? MLBA_BLUR_FFT : (P->blur_fft_taps ? MLBA_BLUR_FFT_TAPS : MLBA_BLUR_DIRECT);
+}
+
+int mlba_plan_taps_ms(mlba_plan_t P, double* ms_out) {
+    if (!P || !ms_out) return MLBA_EINVAL;
+    for (int i = 0; i < 2; ++i) ms_out[i] = P->taps_ms[i];
+    return MLBA_OK;
 }
 
 int mlba_plan_destroy(mlba_plan_t P) {

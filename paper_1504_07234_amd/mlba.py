@@ -18,7 +18,7 @@ RECT, REFLECT, PERIODIC, ZERO, ANTIREFLECT = (_lib.BC_RECT, _lib.BC_REFLECT, _li
                                              _lib.BC_ANTIREFLECT)
 BCCB, DCT, NONE, AR = _lib.PRECOND_BCCB, _lib.PRECOND_DCT, _lib.PRECOND_NONE, _lib.PRECOND_AR
 MLBA, ALG4, ALG2 = _lib.METHOD_MLBA, _lib.METHOD_ALG4, _lib.METHOD_ALG2
-BLUR_DIRECT, BLUR_FFT = _lib.BLUR_DIRECT, _lib.BLUR_FFT
+BLUR_DIRECT, BLUR_FFT, BLUR_FFT_TAPS = _lib.BLUR_DIRECT, _lib.BLUR_FFT, _lib.BLUR_FFT_TAPS
 
 
 def _stream(stream=None) -> ctypes.c_void_p:
@@ -98,15 +98,20 @@ class Plan:
               "mlba_plan_set_psf")
 
     def set_blur(self, mode: int, stream=None):
-        """BLUR_DIRECT or BLUR_FFT for A and A^T (rectangular model)."""
+        """BLUR_DIRECT, BLUR_FFT or BLUR_FFT_TAPS for A and A^T (see mlba_plan_set_blur)."""
         check(self._lib.mlba_plan_set_blur(self._h, int(mode), _stream(stream)), "mlba_plan_set_blur")
 
     def autotune(self, reps: int = 5, stream=None) -> dict:
-        """Times the direct and the FFT blur and keeps the faster (see mlba_plan_autotune)."""
-        ms = (ctypes.c_double * 4)()
+        """Times the direct and the FFT blur and keeps the faster (see mlba_plan_autotune): blur and
+        direct_ms of the direct form on the matrix cores, blur_taps and taps_ms of the one in the order
+        of the taps.  mode: the choice for set_blur of another plan."""
+        ms, taps = (ctypes.c_double * 4)(), (ctypes.c_double * 2)()
         mode = check(self._lib.mlba_plan_autotune(self._h, int(reps), ms, _stream(stream)), "mlba_plan_autotune")
+        check(self._lib.mlba_plan_taps_ms(self._h, taps), "mlba_plan_taps_ms")
         return {"blur": "fft" if mode == _lib.BLUR_FFT else "direct",
-                "direct_ms": [ms[0], ms[1]], "fft_ms": [ms[2], ms[3]] if ms[2] >= 0 else None}
+                "blur_taps": "direct" if mode == _lib.BLUR_DIRECT else "fft", "mode": mode,
+                "direct_ms": [ms[0], ms[1]], "taps_ms": [taps[0], taps[1]],
+                "fft_ms": [ms[2], ms[3]] if ms[2] >= 0 else None}
 
     def opnorm(self, alpha: float, iters: int = 1000, stream=None) -> float:
         """||A^T P_alpha A|| (Lanczos, at most `iters` steps; power steps for the

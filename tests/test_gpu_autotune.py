@@ -1,0 +1,63 @@
+"""The plan autotuner keeps one choice for the calls whose direct blur runs on the
+matrix cores and one for those in the order of the taps; the mode it returns, set
+on another plan, gives both (a plan tuned and a plan told agree bit for bit)."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1504_07234_amd import _lib, mlba
+from tests._util import announce
+
+pytestmark = pytest.mark.gpu
+
+
+# 2048, p = 25: the grid lies between the two direct forms; 64, p = 9: direct for both;
+# 2048, p = 31: the grid for both
+@pytest.mark.parametrize("n,p", [(2048, 25), (64, 9), (2048, 31)])
+def test_mode_transfers(n, p):
+    announce(f"autotune transfer n={n} p={p}")
+    g = np.random.Generator(np.random.PCG64(p))
+    h = g.uniform(0.1, 1.0, (p, p))
+    psf = torch.as_tensor((h / h.sum()).astype(np.float32)).cuda()
+    y = torch.as_tensor(g.uniform(0.0, 1.0, (n, n)).astype(np.float32)).cuda()
+    with mlba.Plan(n, p, mlba.RECT, mlba.BCCB, 1, psf) as a, mlba.Plan(n, p, mlba.RECT, mlba.BCCB, 1, psf) as b:
+        mode = _lib.load().mlba_plan_autotune(a._h, 3, None, None)
+        assert mode >= 0
+        b.set_blur(mode)
+        for implicit in (False, True):
+            fa, fb = (q.restore(y, alpha=0.1, delta=0.3, iters=2, implicit=implicit)[0] for q in (a, b))
+            assert torch.equal(fa, fb), (mode, implicit)
+        assert torch.equal(a.apply_At(y), b.apply_At(y))
+        u = torch.ones((a.N, a.N), device="cuda")
+        assert torch.equal(a.apply_A(u), b.apply_A(u))
+
+
+def test_report():
+    announce("autotune report")
+    h = torch.full((25, 25), 1.0 / 625, device="cuda")
+    lib = _lib.load()
+    with mlba.Plan(256, 25, mlba.RECT, mlba.BCCB, 1, h) as plan:
+        ms = (ctypes.c_double * 2)()
+        assert lib.mlba_plan_taps_ms(plan._h, ms) == 0 and list(ms) == [-1.0, -1.0]
+        t = plan.autotune(reps=2)
+        direct, fft, taps = sum(t["direct_ms"]), sum(t["fft_ms"]), sum(t["taps_ms"])
+        assert min(t["direct_ms"] + t["fft_ms"] + t["taps_ms"]) > 0.0
+        assert t["blur"] == ("fft" if fft < direct else "direct")
+        assert t["blur_taps"] == ("fft" if fft < direct or fft < taps else "direct")
+        assert t["mode"] == {("direct", "direct"): mlba.BLUR_DIRECT, ("fft", "fft"): mlba.BLUR_FFT,
+                             ("direct", "fft"): mlba.BLUR_FFT_TAPS}[(t["blur"], t["blur_taps"])]
+        for mode in (-1, 3):
+            with pytest.raises(_lib.MLBAError):
+                plan.set_blur(mode)
+
+
+def test_mode_beyond_the_grid():
+    """A side whose grid would exceed 3072: refused with either mode that needs it."""
+    h = torch.full((5, 5), 1.0 / 25, device="cuda")
+    with mlba.Plan(3070, 5, mlba.RECT, mlba.NONE, 1, h) as plan:
+        for mode in (mlba.BLUR_FFT, mlba.BLUR_FFT_TAPS):
+            with pytest.raises(_lib.MLBAError):
+                plan.set_blur(mode)
+        assert plan.autotune(reps=1)["mode"] == mlba.BLUR_DIRECT
