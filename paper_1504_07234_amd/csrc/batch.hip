@@ -356,6 +356,12 @@ int mlba_batch_create(mlba_batch_t* batch, int count, const mlba_plan_t* plans, 
 int mlba_batch_autotune(mlba_batch_t B, int reps, mlba_batch_tuning* out, hipStream_t s) {
     if (!B || reps < 1) return MLBA_EINVAL;
     const BatchImage* I = B->imgs;
+    // ordinary values in the scratch: the matrix-core blur treats infinities and NaN
+    // apart and slowly
+    for (BatchImage& d : B->host) {
+        HIPCHK(launch_fill_hash(d.u, (size_t)d.N * d.N, 1u, s));
+        HIPCHK(launch_fill_hash(d.t, (size_t)d.n * d.n, 2u, s));
+    }
     // A and A^T: one or two output rows per thread
     for (int which = 0; which < 2; ++which) {
         double best = 1e300;

@@ -1118,6 +1118,10 @@ int mlba_plan_autotune(mlba_plan_t P, int reps, double* ms_out, hipStream_t s) {
     const int keep[2] = {P->blur_fft, P->blur_fft_taps};
     const int have_fft = ensure_fftconv(P, s);
     if (have_fft < 0 && have_fft != MLBA_EUNSUPPORTED) return have_fft;
+    // ordinary values: what the scratch happens to hold may be infinite or NaN, which
+    // the matrix-core blur treats apart and slowly
+    HIPCHK(launch_fill_hash(P->u, NN(P), 1u, s));
+    HIPCHK(launch_fill_hash(P->t, (size_t)P->n * P->n, 2u, s));
     for (int mode = 0; mode < 3; ++mode) {
         if (mode == 1 && have_fft != MLBA_OK) continue;
         const bool taps = mode == 2;

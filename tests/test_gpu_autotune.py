@@ -61,3 +61,32 @@ def test_mode_beyond_the_grid():
             with pytest.raises(_lib.MLBAError):
                 plan.set_blur(mode)
         assert plan.autotune(reps=1)["mode"] == mlba.BLUR_DIRECT
+
+
+
+@pytest.mark.parametrize("n,p,mode", [(64, 9, 0), (2048, 25, 2), (2048, 31, 1), (512, 17, 0)])
+def test_choice_does_not_hang_on_the_scratch(n, p, mode):
+    """Forms that lie far apart (the grid takes 3, 2, 0.7 and 2.6 times the matrix cores' time): NaN that
+    an earlier restoration left in the plan's buffers does not turn the choice."""
+    announce(f"autotune choice n={n} p={p}")
+    h = torch.full((p, p), 1.0 / p ** 2, device="cuda")
+    with mlba.Plan(n, p, mlba.RECT, mlba.BCCB, 1, h) as plan:
+        assert plan.autotune()["mode"] == mode
+        plan.restore(torch.full((n, n), float("nan"), device="cuda"), alpha=0.1, delta=0.3, iters=2, implicit=True)
+        assert plan.autotune()["mode"] == mode
+
+
+def test_batch_choice_does_not_hang_on_the_scratch():
+    announce("batch autotune after NaN")
+    h = torch.full((15, 15), 1.0 / 225, device="cuda")
+    plans = [mlba.Plan(512, 15, mlba.RECT, mlba.BCCB, 1, h) for _ in range(2)]
+    with mlba.Batch(plans, max_iters=2) as batch:
+        batch.autotune()
+        a = batch.autotune()["conv_ms"]
+        batch.restore([torch.full((512, 512), float("nan"), device="cuda")] * 2, alpha=0.1, delta=0.3, iters=2,
+                      implicit=True)
+        b = batch.autotune()["conv_ms"]
+        for x, y in zip(a, b):
+            assert min(y) < 3.0 * min(x)  # the treatment of NaN takes 20 times as long
+    for p in plans:
+        p.close()
