@@ -274,20 +274,56 @@ __device__ __forceinline__ double conv_put4(const ConvJob& j, int y, int x, f32x
     return ss;
 }
 
-// Plain tap loop over the tile, from global memory.
-__device__ __forceinline__ double conv_tile_taps(const ConvJob& j, int P, int flip, int TY, int oy0, int ox0) {
+// Plain tap loop over the tile, for a window that the split cannot hold: the
+// values themselves take the split ones' place in LDS.  A thread owns four or
+// eight columns of a row; eight taps at a time meet a segment of them.  With
+// every value read from global memory instead, a restoration whose state had
+// become NaN took 35 times as long (512 x 512, p = 15: 287 us a blur).
+template <int KC, int R>
+__device__ __forceinline__ double conv_tile_taps(const ConvJob& j, int P, int flip, int oy0, int ox0, float* win) {
+    constexpr int TY = conv_ty(R), C = conv_cols(KC), LS = C + 1;  // an odd stride: rows start on distinct banks
+    static_assert(LS * sizeof(float) <= conv_row_elems(KC) * sizeof(__bf16), "fits the split window");
+    const int rows = TY + P - 1, cols = CONV_TX + P - 1;
+    for (int ly = (int)threadIdx.x >> 6; ly < rows; ly += kBlock / 64)
+        for (int lx = threadIdx.x & 63; lx < cols; lx += 64)
+            win[ly * LS + lx] = fetch_ext(j.src, j.S, oy0 + j.org + ly, ox0 + j.org + lx, j.ext);
+    __syncthreads();
+    constexpr int E = R == 1 ? 4 : 8;  // columns of a thread
     double ss = 0.0;
-    for (int i = threadIdx.x; i < TY * CONV_TX; i += kBlock) {
-        const int y = oy0 + i / CONV_TX, x = ox0 + i % CONV_TX;
-        if (y >= j.D || x >= j.D) continue;
-        float v = 0.0f;
 #pragma unroll 1
-        for (int a = 0; a < P; ++a)
+    for (int i = threadIdx.x; i < TY * (CONV_TX / E); i += kBlock) {
+        const int ly = i / (CONV_TX / E), lx = E * (i % (CONV_TX / E));
+        float acc[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = 0.0f;
 #pragma unroll 1
-            for (int b = 0; b < P; ++b)
-                v = fmaf(j.psf[flip ? P * P - 1 - (a * P + b) : a * P + b],
-                         fetch_ext(j.src, j.S, y + j.org + a, x + j.org + b, j.ext), v);
-        ss += conv_put(j, y, x, v);
+        for (int a = 0; a < P; ++a) {
+            const float* row = win + (ly + a) * LS + lx;
+            const float* tap = j.psf + (flip ? P * P - 1 - a * P : a * P);
+            int b = 0;
+#pragma unroll 1
+            for (; b + 8 <= P; b += 8) {
+                float v[E + 7], t[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) t[k] = tap[flip ? -(b + k) : b + k];
+#pragma unroll
+                for (int k = 0; k < E + 7; ++k) v[k] = row[b + k];
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) acc[e] = fmaf(t[k], v[k + e], acc[e]);
+            }
+#pragma unroll 1
+            for (; b < P; ++b) {
+                const float t = tap[flip ? -b : b];
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = fmaf(t, row[b + e], acc[e]);
+            }
+        }
+        const int y = oy0 + ly;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (y < j.D && ox0 + lx + e < j.D) ss += conv_put(j, y, ox0 + lx + e, acc[e]);
     }
     return ss;
 }
@@ -396,7 +432,7 @@ __device__ __forceinline__ double conv_tile(const ConvJob& j, int P, int flip, i
     if (top >= CONV_LEAST) large = 1;
     else if (top > 0) some = 1;
     __syncthreads();
-    return bad || (some && !large) ? conv_tile_taps(j, P, flip, conv_ty(R), oy0, ox0)
+    return bad || (some && !large) ? conv_tile_taps<KC, R>(j, P, flip, oy0, ox0, (float*)win)
                                    : conv_products<KC, R>(j, P, oy0, ox0, win);
 }
 
