@@ -356,9 +356,16 @@ int mlba_batch_create(mlba_batch_t* batch, int count, const mlba_plan_t* plans, 
 int mlba_batch_autotune(mlba_batch_t B, int reps, mlba_batch_tuning* out, hipStream_t s) {
     if (!B || reps < 1) return MLBA_EINVAL;
     const BatchImage* I = B->imgs;
-    // ordinary values in the scratch: the matrix-core blur treats infinities and NaN
-    // apart and slowly
-    for (BatchImage& d : B->host) {
+    // the plans' scratch in place of the last restoration's observation and state, with
+    // ordinary values: the matrix-core blur treats infinities and NaN apart and slowly
+    for (int i = 0; i < B->count; ++i) {
+        BatchImage& d = B->host[i];
+        d.g = nullptr;
+        d.z = B->plans[i]->z;
+        d.zin = d.z;
+        d.w = B->plans[i]->w;
+        d.blur_acc = 0;
+        d.state_planes = d.bands;
         HIPCHK(launch_fill_hash(d.u, (size_t)d.N * d.N, 1u, s));
         HIPCHK(launch_fill_hash(d.t, (size_t)d.n * d.n, 2u, s));
     }

@@ -90,3 +90,31 @@ def test_batch_choice_does_not_hang_on_the_scratch():
             assert min(y) < 3.0 * min(x)  # the treatment of NaN takes 20 times as long
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("implicit", [False, True])
+def test_batch_tuner_leaves_the_state(implicit):
+    """The tuner after a restoration with the caller's state: it reads and writes the plans' scratch, not
+    the last call's buffers, and the next call carries on as without it."""
+    announce(f"batch autotune after a restoration, implicit={implicit}")
+    g = np.random.Generator(np.random.PCG64(5))
+    h = torch.as_tensor(g.uniform(0.1, 1.0, (9, 9)).astype(np.float32) / 45).cuda()
+    ys = [torch.as_tensor(g.uniform(0.0, 1.0, (n, n)).astype(np.float32)).cuda() for n in (64, 96)]
+    got = []
+    for tune in (False, True):
+        plans = [mlba.Plan(y.shape[0], 9, mlba.RECT, mlba.BCCB, 2, h) for y in ys]
+        zs = [torch.zeros((p.N, p.N) if implicit else (p.bands, p.N, p.N), device="cuda") for p in plans]
+        with mlba.Batch(plans, max_iters=3) as batch:
+            args = dict(alpha=0.1, mu=1e-3, delta=0.3, iters=3, implicit=implicit)
+            batch.restore(ys, zs=zs, **args)
+            torch.cuda.synchronize()
+            before = [z.clone() for z in zs]
+            if tune:
+                batch.autotune(reps=2)
+                assert all(torch.equal(a, b) for a, b in zip(before, zs))
+            outs, _ = batch.restore(ys, zs=zs, **args)
+            torch.cuda.synchronize()
+            got.append([o.clone() for o in outs])
+        for p in plans:
+            p.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
