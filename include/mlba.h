@@ -376,6 +376,10 @@ int mlba_batch_restore(mlba_batch_t batch, const float* const* g, const double* 
  *     workgroup, or the built-in choice per size (cap 0);
  *   - its column pass: at most 1, 2, 4, 8 or 16 columns per workgroup, or
  *     the built-in choice (cap 0).
+ * The caps reach the BCCB and DCT passes of sides other than 2^a and 3 2^a from
+ * 64 to 1536, whose transforms are compiled with a batching of their own.  A
+ * batch without such a side keeps the caps at 0, and the one time stands for
+ * every cap.
  * The timed launches only write the plans' scratch buffers (residual,
  * spectral workspace, A^T output), never a state.  A captured graph is
  * dropped and re-captured by the next graph restore.  Results do not depend on

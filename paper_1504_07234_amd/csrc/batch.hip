@@ -392,11 +392,19 @@ int mlba_batch_autotune(mlba_batch_t B, int reps, mlba_batch_tuning* out, hipStr
         B->conv_ry[which] = best_ry;
     }
     if (B->precond != MLBA_PRECOND_NONE) {
+        // The caps reach only images whose transforms run on the run-time plan: with
+        // none, every candidate is the same launch, timed once.
+        bool capped = false;
+        for (const BatchImage& d : B->host) capped = capped || precond_takes_caps(d);
         // row passes (forward and inverse): caps on the row pairs per workgroup
         static const int rows_cand[MLBA_TUNE_ROWS] = {0, 1, 2, 4};
         double best = 1e300;
         int best_w = 0;
         for (int c = 0; c < MLBA_TUNE_ROWS; ++c) {
+            if (c > 0 && !capped) {
+                if (out) out->rows_ms[c] = best;
+                continue;
+            }
             B->rows_want = rows_cand[c];
             STCHK(configure(B, s));
             double ms = 0.0;
@@ -418,6 +426,10 @@ int mlba_batch_autotune(mlba_batch_t B, int reps, mlba_batch_tuning* out, hipStr
         best = 1e300;
         best_w = 0;
         for (int c = 0; c < MLBA_TUNE_COLS; ++c) {
+            if (c > 0 && !capped) {
+                if (out) out->cols_ms[c] = best;
+                continue;
+            }
             B->cols_want = cols_cand[c];
             STCHK(configure(B, s));
             double ms = 0.0;

@@ -1222,6 +1222,8 @@ int fft_seq_shift(int batch) { return seq_shift_for(batch); }
 // ---- batched preconditioner passes ---------------------------------------
 // Workgroup b serves image bmap[b], block b - bfirst[img] of the given pass.
 
+bool precond_takes_caps(const BatchImage& I) { return I.precond < 2 && !seq_length(I.n); }
+
 int precond_pass_tiles(const BatchImage& I, int pass) {
     if (I.precond == 2) return 0;  // P = I: the descriptor aliases t to r
     if (I.precond == 3) return pass == 3 ? 0 : (I.n + 1) / 2;  // antireflective: one row pair per workgroup

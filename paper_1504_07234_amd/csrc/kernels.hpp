@@ -463,6 +463,8 @@ int fft_rows_batch_at_most(int n, int want);
 int fft_cols_batch_at_most(int n, int want);
 // batched preconditioner passes: pass 0 rows forward, 1 columns, 2 rows inverse
 int precond_pass_tiles(const BatchImage& I, int pass);
+// whether the batching caps reach the image's transform passes
+bool precond_takes_caps(const BatchImage& I);
 // pass 3: columns, inverse FFT only, of the real dense spectrum I.eacc (into swork)
 hipError_t launch_precond_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks,
                                   int pass, int precond, int nmax, hipStream_t s,

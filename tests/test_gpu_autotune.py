@@ -118,3 +118,22 @@ def test_batch_tuner_leaves_the_state(implicit):
         for p in plans:
             p.close()
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("sides,kind,bc", [((64, 96, 512), mlba.BCCB, mlba.RECT), ((64, 768), mlba.DCT, mlba.REFLECT),
+                                           ((65, 129), mlba.AR, mlba.ANTIREFLECT), ((80, 96), mlba.BCCB, mlba.RECT)])
+def test_batch_caps(sides, kind, bc):
+    """The batching caps are searched where some image's transform takes them (80 = 2^4 5)."""
+    announce(f"batch caps {sides} kind={kind}")
+    h = torch.full((5, 5), 1.0 / 25, device="cuda")
+    plans = [mlba.Plan(n, 5, bc, kind, 1, h) for n in sides]
+    with mlba.Batch(plans, max_iters=2) as batch:
+        t = batch.autotune(reps=2)
+    for p in plans:
+        p.close()
+    times = t["rows_ms"], t["cols_ms"]
+    assert min(times[0] + times[1]) > 0.0
+    if 80 in sides:
+        assert all(len(set(x)) > 1 for x in times)
+    else:
+        assert (t["fft_rows_cap"], t["fft_cols_cap"]) == (0, 0) and all(len(set(x)) == 1 for x in times)
