@@ -30,10 +30,9 @@
 //
 // bfloat16 has float32's exponent range, so nothing is scaled.  What the split
 // cannot hold takes the plain tap loop:
-//   - a window or a PSF with a value that is not finite in bfloat16 (infinities
-//     and NaN reach exactly the outputs whose taps touch them);
-//   - values so large that the sum of the rounded first parts could overflow
-//     where the blur does not;
+//   - infinities, NaN and values above bfloat16's largest, and sums of the rounded
+//     first parts that overflow: some sum of the tile is then not finite.  In the
+//     loop infinities and NaN reach exactly the outputs whose taps touch them;
 //   - a window or a PSF whose largest value is below 2^-95, where the third parts
 //     leave bfloat16's range (2^-133): at 2^-115 the error was 5.6e-7, in the tap
 //     loop 1.5e-7.  A smaller value beside larger ones loses less than 2^-133.
@@ -77,19 +76,17 @@ static int conv_tiles_r(int D, int r) {
     return ((D + CONV_TX - 1) / CONV_TX) * ((D + conv_ty(r) - 1) / conv_ty(r));
 }
 
-// PSF rows a = -1 .. p + CONV_AHEAD (zero outside [0, p)), then one element for
-// the windows these taps can be multiplied with: the bits of the largest value
-// allowed in one, and whether the taps need the plain loop with any of them
-__host__ __device__ constexpr int conv_taps_range(int p) {
+// PSF rows a = -1 .. p + CONV_AHEAD (zero outside [0, p)), then one element with
+// whether the taps are too small for the split
+__host__ __device__ constexpr int conv_taps_flag(int p) {
     return (p + 2 + CONV_AHEAD) * CONV_SPLITS * conv_depth(p) * 32;
 }
-size_t conv_taps_elems(int p) { return (size_t)conv_taps_range(p) + 1; }
+size_t conv_taps_elems(int p) { return (size_t)conv_taps_flag(p) + 1; }
 
-constexpr unsigned CONV_LEAST = 0x10000000u;    // 2^-95
-constexpr unsigned CONV_LARGEST = 0x7f7f0000u;  // the largest bfloat16 value
-
-// the bits of |x|: ordered as the values, NaN above infinity
-__device__ __forceinline__ unsigned abs_bits(float x) { return __builtin_bit_cast(unsigned, x) & 0x7fffffffu; }
+// Of the or of some values' bits: whether one of them is 2^-95 or more (the
+// exponents below are the 32 smallest), and whether one is not zero.
+__device__ __forceinline__ bool conv_any_large(unsigned bits) { return (bits & 0x70000000u) != 0; }
+__device__ __forceinline__ bool conv_any(unsigned bits) { return (bits & 0x7fffffffu) != 0; }
 
 __device__ __forceinline__ void split3(float x, __bf16* h) {
     h[0] = (__bf16)x;
@@ -115,20 +112,11 @@ __global__ __launch_bounds__(64) void conv_taps_kernel(const float* __restrict__
         }
     }
     if (blockIdx.x == 0 && blockIdx.y == 0) {
-        unsigned top = 0;
-        float sum = 0.0f;
-        for (int i = threadIdx.x; i < p * p; i += 64) {
-            top = max(top, abs_bits(psf[i]));
-            sum += fabsf(psf[i]);
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-            top = max(top, (unsigned)__shfl_xor((int)top, off, 64));
-            sum += __shfl_xor(sum, off, 64);
-        }
-        const bool plain = top > CONV_LARGEST || (top > 0 && top < CONV_LEAST);
-        const unsigned most = min(CONV_LARGEST, abs_bits(0x1p126f / sum));
+        unsigned bits = 0;
+        for (int i = threadIdx.x; i < p * p; i += 64) bits |= __builtin_bit_cast(unsigned, psf[i]);
+        const bool tiny = __any(conv_any(bits)) && !__any(conv_any_large(bits));
         if (threadIdx.x < 2)
-            (threadIdx.x ? taps1 : taps0)[conv_taps_range(p)] = make_uint4(most, plain ? 1u : 0u, 0u, 0u);
+            (threadIdx.x ? taps1 : taps0)[conv_taps_flag(p)] = make_uint4(tiny ? 1u : 0u, 0u, 0u, 0u);
     }
     const int a = (int)blockIdx.x - 1, q = blockIdx.y, flip = threadIdx.x >> 5, l = threadIdx.x & 31;
     bf16x8 f[CONV_SPLITS];
@@ -158,14 +146,14 @@ struct __attribute__((packed, aligned(4))) FloatQuad {
     float v[4];
 };
 
-// Splits four values into the rows of the window; top: the largest abs_bits seen.
+// Splits four values into the rows of the window; bits collects the or of theirs.
 template <int C>
-__device__ __forceinline__ void conv_put_split(__bf16* win, const float* v, unsigned* top) {
+__device__ __forceinline__ void conv_put_split(__bf16* win, const float* v, unsigned* bits) {
     unsigned w[CONV_SPLITS][2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         float r0 = v[2 * e], r1 = v[2 * e + 1];
-        *top = max(*top, max(abs_bits(r0), abs_bits(r1)));
+        *bits |= __builtin_bit_cast(unsigned, r0) | __builtin_bit_cast(unsigned, r1);
 #pragma unroll
         for (int s = 0; s < CONV_SPLITS; ++s) {
             w[s][e] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
@@ -217,7 +205,7 @@ __device__ __forceinline__ void conv_fetch(const ConvJob& j, int P, int TY, int 
     }
 }
 
-// Returns the largest abs_bits of the thread's values.  A window that leaves the
+// Returns the or of the bits of the thread's values.  A window that leaves the
 // image under the antireflective extension (up to four sources a value) is read
 // here, row by row.
 template <int KC, int U>
@@ -227,22 +215,22 @@ __device__ __forceinline__ unsigned conv_commit(const ConvJob& j, int P, int TY,
     const int rows = TY + P - 1;
     const int lx = 4 * ((int)threadIdx.x & 31), ly0 = (int)threadIdx.x >> 5;
     const int S = j.S, y0 = oy0 + j.org, x0 = ox0 + j.org;
-    unsigned top = 0;
-    if (lx >= C) return top;
+    unsigned bits = 0;
+    if (lx >= C) return bits;
     if (j.ext == EXT_ANTIREFLECT && !(y0 >= 0 && x0 >= 0 && y0 + rows <= S && x0 + C <= S)) {
 #pragma unroll 1
         for (int ly = ly0; ly < rows; ly += RS) {
             float q[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) q[e] = fetch_antireflect(j.src, S, y0 + ly, x0 + lx + e);
-            conv_put_split<C>(win + ly * LS + lx, q, &top);
+            conv_put_split<C>(win + ly * LS + lx, q, &bits);
         }
-        return top;
+        return bits;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (ly0 + u * RS < rows) conv_put_split<C>(win + (ly0 + u * RS) * LS + lx, v[u], &top);
-    return top;
+        if (ly0 + u * RS < rows) conv_put_split<C>(win + (ly0 + u * RS) * LS + lx, v[u], &bits);
+    return bits;
 }
 
 // dst = g - v (returning v's square sum), dst + v or v
@@ -259,18 +247,22 @@ __device__ __forceinline__ double conv_put(const ConvJob& j, int y, int x, float
     return ss;
 }
 
-// the same for four columns on 16-byte boundaries
+// the same for four columns.  A side that is no multiple of four puts the rows off
+// the 16-byte boundaries; one access of four bytes' alignment still takes half of
+// what four accesses take (A^T at 1024 x 1024, p = 7: 11.4 -> 9.9 us; 2048 x 2048,
+// p = 3: 21.1 -> 16.5).
 __device__ __forceinline__ double conv_put4(const ConvJob& j, int y, int x, f32x4 v) {
+    typedef f32x4 __attribute__((aligned(4))) Quad;
     const size_t i = (size_t)y * j.D + x;
     double ss = 0.0;
     if (j.g) {
-        v = *(const f32x4*)(j.g + i) - v;
+        v = *(const Quad*)(j.g + i) - v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) ss += (double)v[e] * (double)v[e];
     } else if (j.acc) {
-        v = *(const f32x4*)(j.dst + i) + v;
+        v = *(const Quad*)(j.dst + i) + v;
     }
-    *(f32x4*)(j.dst + i) = v;
+    *(Quad*)(j.dst + i) = v;
     return ss;
 }
 
@@ -328,10 +320,13 @@ __device__ __forceinline__ double conv_tile_taps(const ConvJob& j, int P, int fl
     return ss;
 }
 
-// The outputs of the tile whose split window is in LDS.  Returns the thread's
-// sum of squares of the residuals it wrote (0 without g).
+// The sums of the tile whose split window is in LDS: v[i] holds those of the lane's
+// block in row pair i (conv_store).  Returns whether all are finite: an infinity, a
+// NaN or a value above bfloat16's largest in the window or the taps gives NaN (its
+// first part meets a zero of T_t or its own second part), and where the rounded
+// first parts overflow, infinity.
 template <int KC, int R>
-__device__ __forceinline__ double conv_products(const ConvJob& j, int P, int oy0, int ox0, const __bf16* win) {
+__device__ __forceinline__ bool conv_products(const ConvJob& j, int P, const __bf16* win, f32x4 (&v)[R]) {
     constexpr int C = conv_cols(KC), LS = conv_row_elems(KC), S = CONV_SPLITS;
     constexpr int NF = R == 1 ? 4 : 2 * R;  // rolling window rows
     constexpr int NT = R == 4 ? 2 : 4;      // rolling tap rows
@@ -392,21 +387,35 @@ __device__ __forceinline__ double conv_products(const ConvJob& j, int P, int oy0
         taps = j.taps + 32;
     }
 
+    float zero = 0.0f;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        v[i] = acc[i] + low[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zero = fmaf(v[i][e], 0.0f, zero);
+    }
+    return zero == 0.0f;
+}
+
+// Writes the tile's outputs.  Returns the thread's sum of squares of the residuals
+// (0 without g).
+template <int R>
+__device__ __forceinline__ double conv_store(const ConvJob& j, int oy0, int ox0, const f32x4 (&v)[R]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int seg = lane & 7, rb = (lane >> 3) & 1, kg = lane >> 4;
     // lane: output block (seg, rb), rows 2 i + (kg >> 1), columns 4 (kg & 1) .. + 3
+    const int x = ox0 + 8 * seg + 4 * (kg & 1), row0 = wave * 4 * R + rb * 2 * R;
     double ss = 0.0;
-    const int x = ox0 + 8 * seg + 4 * (kg & 1);
-    const bool quads = (j.D & 3) == 0 && (((size_t)j.dst | (size_t)j.g) & 15) == 0;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         const int y = oy0 + row0 + 2 * i + (kg >> 1);
         if (y < j.D) {
-            const f32x4 v = acc[i] + low[i];
-            if (quads) {
-                if (x < j.D) ss += conv_put4(j, y, x, v);
+            if (x + 4 <= j.D) {
+                ss += conv_put4(j, y, x, v[i]);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (x + e < j.D) ss += conv_put(j, y, x + e, v[e]);
+                    if (x + e < j.D) ss += conv_put(j, y, x + e, v[i][e]);
             }
         }
     }
@@ -419,21 +428,25 @@ __device__ __forceinline__ double conv_tile(const ConvJob& j, int P, int flip, i
     constexpr int PMAX = KC == 1 ? CONV_K1 : CONV_PMAX;
     constexpr int U = (conv_ty(R) + PMAX - 1 + 7) / 8;
     __shared__ int bad, large, some;
-    const uint4 range = j.taps[conv_taps_range(P)];
+    const unsigned tiny = j.taps[conv_taps_flag(P)].x;
     if (threadIdx.x == 0) {
-        bad = range.y;
+        bad = tiny;
         large = some = 0;
     }
-    float v[U][4];
-    conv_fetch<KC, U>(j, P, conv_ty(R), oy0, ox0, v);
+    float w[U][4];
+    conv_fetch<KC, U>(j, P, conv_ty(R), oy0, ox0, w);
     __syncthreads();
-    const unsigned top = conv_commit<KC, U>(j, P, conv_ty(R), oy0, ox0, v, win);
-    if (top > range.x) bad = 1;
-    if (top >= CONV_LEAST) large = 1;
-    else if (top > 0) some = 1;
+    const unsigned bits = conv_commit<KC, U>(j, P, conv_ty(R), oy0, ox0, w, win);
+    if (conv_any_large(bits)) large = 1;
+    else if (conv_any(bits)) some = 1;
     __syncthreads();
-    return bad || (some && !large) ? conv_tile_taps<KC, R>(j, P, flip, oy0, ox0, (float*)win)
-                                   : conv_products<KC, R>(j, P, oy0, ox0, win);
+    if (large || !some) {
+        f32x4 v[R];
+        if (!conv_products<KC, R>(j, P, win, v)) bad = 1;
+        __syncthreads();
+        if (!bad) return conv_store<R>(j, oy0, ox0, v);
+    }
+    return conv_tile_taps<KC, R>(j, P, flip, oy0, ox0, (float*)win);
 }
 
 // ---- single-image kernels -----------------------------------------------
