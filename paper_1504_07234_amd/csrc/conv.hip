@@ -464,11 +464,15 @@ __global__ __launch_bounds__(kBlock, 3) void conv_kernel(ConvJob j, int P, int f
     }
 }
 
-// Row pairs per lane of a D x D output: the deepest tile that still gives the
-// chip two workgroups per CU.
+// Row pairs per lane of a D x D output: the deepest tile that still leaves most CUs
+// two workgroups.  Two pairs from 400 tiles: A / A^T at 900 x 900, 435 tiles or 855
+// of one pair: p = 7: 7.9 / 8.3 and 8.9 / 9.1 us, p = 31: 20.9 / 21.7 and 28.5 /
+// 30.4; 768 x 768, 288 or 576: p = 3: 6.8 / 7.1 and 6.5 / 6.7, p = 7: even.  Four
+// from 512: with them an iteration of 1280 x 1280, 400 tiles, takes 90.1 / 99.0 us
+// (p = 3 / 15), with two 86.1 / 95.2.
 static int conv_default_r(int D, int p) {
     int r = conv_max_r(p);
-    while (r > 1 && conv_tiles_r(D, r) < 512) r /= 2;
+    while (r > 1 && conv_tiles_r(D, r) < (r == 4 ? 512 : 400)) r /= 2;
     return r;
 }
 
