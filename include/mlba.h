@@ -211,8 +211,9 @@ int mlba_plan_destroy(mlba_plan_t plan);
  * MLBA_BLUR_DIRECT (default): LDS-tiled direct convolution, p^2 taps per
  * output.  The calls whose result hangs on the order of that sum keep the
  * order of the taps: eq. (MLBA2) with the explicit state, mlba_apply_A and
- * mlba_residual.  The others (the implicit state, Algorithms 2 and 4 with
- * either state, mlba_apply_At, the norm estimates) run on the matrix cores.
+ * mlba_residual; so does mlba_apply_At for p <= 7.  The others (the implicit state, Algorithms 2 and 4 with
+ * either state, mlba_apply_At for p > 7, the norm estimates) run on the matrix
+ * cores.
  * MLBA_BLUR_FFT: circular convolution on an M x M grid, M >= m =
  * n + p - 1, M = 2^a 3^b (section 2.1's FFT evaluation), three passes per
  * product: row transforms, a column pass, inverse row transforms.
