@@ -26,6 +26,7 @@ namespace mlba {
 constexpr int PC_TY = 32;       // rows of a tile of the observed grid
 constexpr int PC_TX = 64;       // columns
 constexpr int PC_TS = PC_TX + 4;  // LDS row stride of the t and rbar tiles: 16 rows on distinct banks
+constexpr int PC_WCOLS = 128;     // most columns of a window, two rows at a time
 
 typedef float corr_f32x4 __attribute__((ext_vector_type(4)));
 
@@ -100,13 +101,13 @@ __global__ __launch_bounds__(kBlock) void psf_corr_batched_kernel(const BatchIma
         dv[k] = c;
     }
     {
-        const int lx = threadIdx.x & 127, x = ox0 + lx - cs.padl, ly0 = (int)threadIdx.x >> 7;
+        const int lx = threadIdx.x % PC_WCOLS, x = ox0 + lx - cs.padl, ly0 = (int)threadIdx.x / PC_WCOLS;
         const bool col = lx < cs.wc && x >= 0 && x < N;
-        for (int l0 = ly0; l0 < cs.wr; l0 += WU * (kBlock / 128)) {
+        for (int l0 = ly0; l0 < cs.wr; l0 += WU * (kBlock / PC_WCOLS)) {
             float w[WU], u[WU];
 #pragma unroll
             for (int k = 0; k < WU; ++k) {
-                const int y = oy0 + l0 + k * (kBlock / 128);
+                const int y = oy0 + l0 + k * (kBlock / PC_WCOLS);
                 const bool in = col && y < N;
                 const size_t o = in ? (size_t)y * N + x : 0;
                 w[k] = wbar[o];
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void psf_corr_batched_kernel(const BatchIma
             }
 #pragma unroll
             for (int k = 0; k < WU; ++k) {
-                const int ly = l0 + k * (kBlock / 128);
+                const int ly = l0 + k * (kBlock / PC_WCOLS);
                 if (lx < cs.wc && ly < cs.wr) {
                     Wl[ly * cs.wc + lx] = w[k];
                     Ul[ly * cs.wc + lx] = u[k];
@@ -185,7 +186,8 @@ hipError_t launch_psf_corr_batched(const BatchImage* imgs, const int* bmap, cons
                                    int first, double* part, double* apart, hipStream_t s) {
     if (nblocks <= 0) return hipSuccess;
     const size_t lds = corr_lds_floats(p) * sizeof(float);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    // 128 columns of the window are staged (p <= 49)
+    if (lds > 160 * 1024 || corr_shape(p).wc > PC_WCOLS) return hipErrorInvalidValue;
     hipLaunchKernelGGL(psf_corr_batched_kernel, dim3(nblocks), dim3(kBlock), lds, s, imgs, bmap, bfirst, first,
                        part, apart);
     return hipGetLastError();
