@@ -6,7 +6,7 @@
 
 namespace mlba {
 
-constexpr int kBlock = 256;  // threads per workgroup for every kernel here
+constexpr int kBlock = 256;  // threads of a workgroup, unless a kernel says otherwise
 
 // Boundary extension applied when a kernel reads outside [0, S):
 //   EXT_ZERO     value 0
@@ -124,7 +124,8 @@ __device__ __forceinline__ void xcd_tile(int* bx, int* by) {
     *bx = l - *by * gx;
 }
 
-// Wave-level then workgroup-level sum of a double (blockDim.x == kBlock).
+// Wave-level then workgroup-level sum of a double (whole waves, at most kBlock
+// threads).
 __device__ __forceinline__ double block_sum(double v, double* smem /* >= kBlock/64 */) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;

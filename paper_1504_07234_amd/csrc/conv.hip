@@ -6,16 +6,26 @@
 // Every float32 value x is split into three bfloat16 parts x = x1 + x2 + x3
 // (8 + 8 + 8 significand bits: the sum is x itself), the window's while it is
 // staged, the taps' when the PSF is set.  A product of the blur is then the
-// six products x1 h1, x1 h2, x2 h1, x2 h2, x1 h3, x3 h1 (exact in float32; what
-// is left out is below 2^-25 of |x h|), summed in float32 by
-// v_mfma_f32_16x16x32_bf16: 6 x 16 cycles for the work of 16 x 16 x 32
-// multiply-adds, against 512 cycles of vector FMAs.
+// six products x1 h1, x1 h2, x2 h1, x2 h2, x1 h3, x3 h1 (each exact in float32;
+// the three left out are below 2^-24 of |x h|, as a rule below 2^-27), summed in
+// float32 by v_mfma_f32_16x16x32_bf16: 6 x 16 cycles for the work of 16 x 16 x 32
+// multiply-adds, against 512 cycles of vector FMAs.  x1 h1, the bulk of the sum,
+// is added up apart from the rest and loses few bits, so the result is nearer to
+// the exact one than a chain of FMAs.  Error of A^T in the 2-norm, FMAs -> here,
+// 1024 x 1024, units of 1e-8:
+//                        p = 3           p = 9         p = 17         p = 31
+//   Gaussian           5.7 -> 3.0     16.2 -> 8.1   30.4 -> 13.0   55.3 -> 22.7
+//   disk               4.4 -> 2.6     12.6 -> 3.8   25.2 ->  5.5   47.5 -> 13.0
+//   random             5.0 -> 2.7     16.2 -> 5.4   29.4 ->  8.8   54.9 -> 17.3
+//   streak             4.4 -> 2.7      7.2 -> 3.0    9.7 ->  3.9   13.3 ->  4.5
+//   a row or a column  3.6 -> 2.7      5.7 -> 2.7    7.6 ->  3.0   10.1 ->  2.7
+//   one tap            2.51 -> 2.54   2.52 -> 2.55  2.52 -> 2.54   2.52 -> 2.54
 //
 // One matrix product: D[m][s] += T_t[m][k] X_t[k][s].  A column s of D is a
 // block of 2 rows x 8 columns of outputs (m = 8 yr + xo), X_t[k][s] the input
 // row t under it from its first column on, and T_t[m][k] = tap(t - yr, k - xo)
 // (zero outside the PSF), so p + 1 products of depth K = 8 + p - 1 (padded to
-// 32 up to p = 25, to 64 up to p = 57) give the 256 outputs of D.  A wave
+// 32 up to p = 25, to 64 up to CONV_PMAX = 49) give the 256 outputs of D.  A wave
 // holds R such D's, one below the other: an input row is read from LDS once
 // and used by the R of them through a rolling window of 2 R rows in
 // registers, and the fragments of T_t, laid out in the order of the lanes when
@@ -24,9 +34,11 @@
 //
 // The products run at the rate of the matrix cores (4096 x 4096, p = 15: 42 us
 // without the staging), the staging and its split add to that, in series (30
-// us).  With vector FMAs in the order of the taps A^T took 43 / 92 us at 2048 x
-// 2048, p = 15 / 25, now 33 / 38 (the relative error 1.2e-7 / 1.8e-7 instead of
-// 2.5e-7 / 4.2e-7).
+// us).  A and A^T with vector FMAs in the order of the taps -> here, on random
+// values (on zeros the matrix cores are up to a fifth faster), us: 512 x 512, p =
+// 15: 11.0 / 11.5 -> 6.4 / 7.9; 1024 x 1024, p = 15 / 31: 15.2 / 18.1 -> 10.5 / 12.1
+// and 40.7 / 52.7 -> 22.4 / 28.1; 2048 x 2048: 38.5 / 44.1 -> 25.0 / 25.8 and 126 /
+// 139 -> 73 / 73.
 //
 // bfloat16 has float32's exponent range, so nothing is scaled.  What the split
 // cannot hold takes the plain tap loop:

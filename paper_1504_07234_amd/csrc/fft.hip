@@ -608,7 +608,8 @@ __global__ __launch_bounds__(kBlock) void fft_cols_residual_kernel(float2* __res
 // to the rows it reads and transforms the new res; the inverse row pass
 // writes z = P res with the partial sums of res . z per workgroup.  The
 // arithmetic of every value is that of the separate update and dot kernels.
-// The update of Algorithm 2's vectors at flat index i.  Bound by memory (six
+
+// The forward pass's update at flat index i.  Bound by memory (six
 // vectors); with each element's stores in front of the next one's loads a row
 // was a chain of round trips: 16.7 -> 9.0 us at 1024 x 1024.
 struct PcgSource {

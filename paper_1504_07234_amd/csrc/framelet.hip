@@ -344,9 +344,9 @@ static hipError_t launch_syn(const float* zlev, const float* low, int N, float* 
 
 hipError_t launch_synthesis_level(const float* zlev, const float* low, int N, int d, float* out, LevelMu mu,
                                   float delta, int thr_low, int thr_bands, hipStream_t s) {
-    // one wave to a workgroup while 256 columns would give no CU two (64 / 400 / 512
-    // / 640 / 1024 columns, three levels: 17.8 / 18.4 / 20.0 / 23.2 / 35.0 us against
-    // 18.8 / 20.0 / 21.9 / 23.6 / 32.7)
+    // one wave to a workgroup while 256 columns would leave some of the 256 CUs without
+    // one (64 / 400 / 512 / 640 / 1024 columns, three levels: 17.8 / 18.4 / 20.0 / 23.2
+    // / 35.0 us against 18.8 / 20.0 / 21.9 / 23.6 / 32.7)
     const bool wide = synthesis_level_tiles(N, d, true) >= 256;
     switch (d) {
         case 1: return wide ? launch_syn<1, kBlock>(zlev, low, N, out, mu, delta, thr_low, thr_bands, s)

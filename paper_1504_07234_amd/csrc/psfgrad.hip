@@ -57,11 +57,11 @@ int psf_corr_tiles(const BatchImage& I) {
 // of the window and the tile's rows r - (p-1) + a give
 //   C[q][a] += sum_x W[r][x + p-1-q] t[r - (p-1) + a][x],
 // 16 lags q by 16 lags a and four pixels per v_mfma_f32_16x16x4_f32 (float32
-// products and sums).  On the vector units the step of 16 images of 256 x 256, p =
-// 15, took 47 us, now 28: the staging of the four tiles and the waves' LDS reads.  With one block of lags (p <= 16) the four waves share
-// the window's rows and add up in LDS; otherwise each wave takes whole blocks.
-// The vector form of this kernel read 46 LDS values for 128 multiply-adds and
-// was bound by them (47 us a step at 16 x 256 x 256, p = 15).
+// products and sums).  With one block of lags (p <= 16) the four waves share the
+// window's rows and add up in LDS; otherwise each wave takes whole blocks.  A step
+// of 16 images of 256 x 256, p = 15, takes 28 us: the staging of the four tiles and
+// the waves' LDS reads.  On the vector units, with 46 LDS values read for 128
+// multiply-adds, it took 47.
 __global__ __launch_bounds__(kBlock) void psf_corr_batched_kernel(const BatchImage* __restrict__ imgs,
                                                                   const int* __restrict__ bmap,
                                                                   const int* __restrict__ bfirst, int first,

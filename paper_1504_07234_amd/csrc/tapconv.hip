@@ -9,11 +9,11 @@
 //     coefficient within rounding of its threshold changes them (another order
 //     moves the gradient of the observations by 6e-5 of its size at 16 x 256 x
 //     256, p = 15, 30 iterations).
-// The implicit state, A^T and the norm estimate use the matrix cores
-// (conv.hip), whose sums are more accurate and at 2048 x 2048 take 21 / 33 / 38 us
-// (p = 5 / 15 / 25) where these take 22 / 43 / 92; 1024 x 1024, p = 49: 47 and 191.
-// Bound by the vector units, 0.78 of their rate at p = 31 (8.1 GFLOP in 131 us at
-// 2048 x 2048), and on small images by the latency of staging the window.
+// The implicit state, A^T for p > 7 and the norm estimates use the matrix cores
+// (conv.hip), whose sums are more accurate and whose A takes 18 / 25 / 73 us at
+// 2048 x 2048 (p = 5 / 15 / 31) where these take 17 / 33 / 98.
+// Bound by the vector units at large p (8.1 GFLOP in those 98 us) and on small
+// images by the latency of staging the window.
 //
 // One workgroup computes a tile of 64 output columns; the input window is
 // staged once in LDS under the requested boundary extension.  Every thread owns
@@ -284,6 +284,10 @@ hipError_t launch_tapconv(const ConvJob& j, int p, int flip, double* partials, i
 // r = g - A u with the residual-norm partial of the tile written to
 // partials[pbase + local tile]; otherwise the A^T correlation.  P > 0: every
 // image has that PSF side (one tap loop in the kernel); P == 0: any sides.
+// One tile height, one row a thread: with two an iteration of the explicit state
+// took as long or longer at every batch measured (32 uneven images 707 us and 731
+// with two rows in both products, 16 x 256 x 256, p = 15: 137 and 148, 8 x 1024 x
+// 1024, p = 15: 518 and 530, p = 25 and 31: even).
 
 template <bool FLIP>
 __device__ __forceinline__ double tap_tile_any(const ConvJob& j, int p, int bx, int by, float* lds) {
