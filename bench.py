@@ -10,7 +10,7 @@ scene, PSF and noise) and resident in HBM before the timed region starts.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
 
-The blur is the one the plan autotuner picks (direct taps or the FFT grid).
+The blur is the one the plan autotuner picks (direct or the FFT grid).
 Prints one JSON line: Mpixel-iter/s over the observed pixels, the per-kernel
 and per-phase breakdown measured with HIP events on the library's stream on
 every 4th iteration of the timed region, the roofline of the dominant kernel
@@ -51,12 +51,12 @@ PROFILE_EVERY = 4              # kernel events on every 4th timed iteration (the
 TRAFFIC = {
     # 2078^2, 3 levels: the three shrink-synthesis launches of one iteration (d = 4, 2, 1)
     ("shrink_synthesis", "fft-implicit"): {
-        "fetch_kib": 43436.0, "write_kib": 50610.5, "fetch_scale": 2.0, "write_scale": 1.0, "launches": 3,
-        "sources_sha256": "813e34e335ba6aa807db16c079922bca08d167c0846a1a5f5c4ece92bfe66b73"},
+        "fetch_kib": 43435.3, "write_kib": 50610.5, "fetch_scale": 2.0, "write_scale": 1.0, "launches": 3,
+        "sources_sha256": "cc652ba8d0e854e5a42d4a6d080fc2ecfd6805670bf0a5606b49cb8d93eeb7d7"},
     # the direct A^T accumulating into omega (p = 31), one launch per iteration
     ("conv_blur_t", "direct-implicit"): {
-        "fetch_kib": 17582.1, "write_kib": 16878.0, "fetch_scale": 2.0, "write_scale": 1.0, "launches": 1,
-        "sources_sha256": "0cadeb24c27af3e487dec833b4026d5eb191001033c0a4f11b519d67bc769782"},
+        "fetch_kib": 18073.1, "write_kib": 16878.0, "fetch_scale": 2.0, "write_scale": 1.0, "launches": 1,
+        "sources_sha256": "073a1b57aaaaa7da1ac4cdacc448044494ba13c51f42005c3a70400e75d5ff0f"},
 }
 # the sources that define each kernel's device code
 TRAFFIC_SOURCES = {

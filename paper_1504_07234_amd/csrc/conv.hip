@@ -32,9 +32,11 @@
 // the PSF is set, are read from global memory (they stay in the caches) one
 // row ahead.  A workgroup's four waves cover 64 columns x 16 R rows.
 //
-// The products run at the rate of the matrix cores (4096 x 4096, p = 15: 42 us
-// without the staging), the staging and its split add to that, in series (30
-// us).  A and A^T with vector FMAs in the order of the taps -> here, on random
+// The products alone run at the rate of the matrix cores (4096 x 4096, p = 15: 42
+// us), the staging and its split add to that, in series (30 us): the matrix cores
+// are busy for 0.15 / 0.34 / 0.62 of the CUs' time (A^T at 512, p = 17; 1024 and
+// 2048, p = 15) and for 0.74 / 0.75 at 2048, p = 25 / 31.  At p > 25 and in the tiles
+// of one or two row pairs 0.43 to 0.47 of the LDS cycles are bank conflicts.  A and A^T with vector FMAs in the order of the taps -> here, on random
 // values (on zeros the matrix cores are up to a fifth faster), us: 512 x 512, p =
 // 15: 11.0 / 11.5 -> 6.4 / 7.9; 1024 x 1024, p = 15 / 31: 15.2 / 18.1 -> 10.5 / 12.1
 // and 40.7 / 52.7 -> 22.4 / 28.1; 2048 x 2048: 38.5 / 44.1 -> 25.0 / 25.8 and 126 /
