@@ -64,6 +64,11 @@ def test_mode_beyond_the_grid():
 
 
 
+def _usual(plan):
+    """The choice of most of three tunings (a pause of the host in one of them may turn it)."""
+    return sorted(plan.autotune()["mode"] for _ in range(3))[1]
+
+
 @pytest.mark.parametrize("n,p,mode", [(64, 9, 0), (2048, 25, 2), (2048, 31, 1), (512, 17, 0)])
 def test_choice_does_not_hang_on_the_scratch(n, p, mode):
     """Forms that lie far apart (the grid takes 3, 2, 0.7 and 2.6 times the matrix cores' time): NaN that
@@ -71,9 +76,9 @@ def test_choice_does_not_hang_on_the_scratch(n, p, mode):
     announce(f"autotune choice n={n} p={p}")
     h = torch.full((p, p), 1.0 / p ** 2, device="cuda")
     with mlba.Plan(n, p, mlba.RECT, mlba.BCCB, 1, h) as plan:
-        assert plan.autotune()["mode"] == mode
+        assert _usual(plan) == mode
         plan.restore(torch.full((n, n), float("nan"), device="cuda"), alpha=0.1, delta=0.3, iters=2, implicit=True)
-        assert plan.autotune()["mode"] == mode
+        assert _usual(plan) == mode
 
 
 def test_batch_choice_does_not_hang_on_the_scratch():
