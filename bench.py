@@ -56,7 +56,7 @@ TRAFFIC = {
     # the direct A^T accumulating into omega (p = 31), one launch per iteration
     ("conv_blur_t", "direct-implicit"): {
         "fetch_kib": 18073.1, "write_kib": 16878.0, "fetch_scale": 2.0, "write_scale": 1.0, "launches": 1,
-        "sources_sha256": "073a1b57aaaaa7da1ac4cdacc448044494ba13c51f42005c3a70400e75d5ff0f"},
+        "sources_sha256": "7f77a8b4dde02734438e69fb2b7aa028f4650aa37eb1e43630371541908ba902"},
 }
 # the sources that define each kernel's device code
 TRAFFIC_SOURCES = {

@@ -232,8 +232,9 @@ int mlba_plan_destroy(mlba_plan_t plan);
  * spectrum on first use (synchronous) and returns MLBA_EUNSUPPORTED when M
  * would exceed 3072.  mlba_plan_autotune: times the grid and both forms of the
  * direct blur on the plan's own scratch buffers (`reps` calls each, HIP
- * events, synchronous), keeps the fastest for either kind of call,
- * writes the mean ms per call to ms_out (host, optional:
+ * events, synchronous), keeps the fastest for either kind of call (the order of
+ * the taps, which rounds most, only where it wins without its tiles for small
+ * images and 1.3 times over), writes the mean ms per call to ms_out (host, optional:
  * direct A, direct A^T on the matrix cores, FFT A, FFT A^T; -1 where
  * unavailable) and returns the mode, which mlba_plan_set_blur takes for another
  * plan of these sizes, or an error.  mlba_plan_taps_ms: the last autotune's ms of

@@ -189,7 +189,10 @@ hipError_t launch_conv_taps(const float* psf, int p, uint4* taps0, uint4* taps1,
 // the same jobs (without accumulation) in the order of the taps on the vector
 // units, for the results that hang on it (tapconv.hip); batched: the tiles of
 // every image in one launch, same_p: every image's PSF side is pmax
-hipError_t launch_tapconv(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s);
+// tall: not the 8-row tiles that an image of tapconv_small takes
+hipError_t launch_tapconv(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s,
+                          bool tall = false);
+bool tapconv_small(int D, int p);
 int tapconv_partials_count(int D);
 int tapconv_batched_tiles(const BatchImage& I, int flip);
 hipError_t launch_tapconv_batched(const BatchImage* imgs, const int* bmap, const int* bfirst, int nblocks, int flip,

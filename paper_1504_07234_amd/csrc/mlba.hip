@@ -233,7 +233,7 @@ int do_blur(mlba_plan_s* P, const float* u, const float* g, float* y, bool want_
     d.g = g;
     d.r = y;
     double* part = want_norm ? P->partials : nullptr;
-    if (taps) HIPCHK(launch_tapconv(blur_job(d), P->p, 1, part, nparts, s));
+    if (taps) HIPCHK(launch_tapconv(blur_job(d), P->p, 1, part, nparts, s, P->taps_tall));
     else HIPCHK(launch_conv_job(blur_job(d), P->p, 1, part, nparts, s));
     MARK(BLUR, CONV_BLUR);
     return MLBA_OK;
@@ -330,7 +330,7 @@ int do_blurT(mlba_plan_s* P, const float* y, float* w, hipStream_t s, bool taps 
     BatchImage d = plan_desc(P);
     d.t = const_cast<float*>(y);
     d.w = w;
-    if (taps) HIPCHK(launch_tapconv(blurT_job(d), P->p, 0, nullptr, nullptr, s));
+    if (taps) HIPCHK(launch_tapconv(blurT_job(d), P->p, 0, nullptr, nullptr, s, P->taps_tall));
     else HIPCHK(launch_conv_job(blurT_job(d), P->p, 0, nullptr, nullptr, s));
     MARK(BLUR_T, CONV_BLUR_T);
     if (P->bc == MLBA_BC_REFLECT) {
@@ -1113,8 +1113,8 @@ int mlba_plan_set_blur(mlba_plan_t P, int mode, hipStream_t s) {
 
 int mlba_plan_autotune(mlba_plan_t P, int reps, double* ms_out, hipStream_t s) {
     if (!P || reps < 1) return MLBA_EINVAL;
-    // [direct / fft / direct in the order of the taps][A / A^T]
-    double t[3][2] = {{0.0, 0.0}, {-1.0, -1.0}, {0.0, 0.0}};
+    // [direct / fft / direct in the order of the taps / that in tall tiles][A / A^T]
+    double t[4][2] = {{0.0, 0.0}, {-1.0, -1.0}, {0.0, 0.0}, {0.0, 0.0}};
     const int keep[2] = {P->blur_fft, P->blur_fft_taps};
     const int have_fft = ensure_fftconv(P, s);
     if (have_fft < 0 && have_fft != MLBA_EUNSUPPORTED) return have_fft;
@@ -1122,25 +1122,33 @@ int mlba_plan_autotune(mlba_plan_t P, int reps, double* ms_out, hipStream_t s) {
     // the matrix-core blur treats apart and slowly
     HIPCHK(launch_fill_hash(P->u, NN(P), 1u, s));
     HIPCHK(launch_fill_hash(P->t, (size_t)P->n * P->n, 2u, s));
-    for (int mode = 0; mode < 3; ++mode) {
+    for (int mode = 0; mode < 4; ++mode) {
         if (mode == 1 && have_fft != MLBA_OK) continue;
-        const bool taps = mode == 2;
+        const bool taps = mode >= 2;
         P->blur_fft = mode == 1;
+        P->taps_tall = mode == 3;
         P->blur_fft_taps = 0;
         // scratch only: u -> r and t -> w of the plan
         int st = time_ms([&]() { return do_blur(P, P->u, nullptr, P->r, false, nullptr, taps, s); }, reps, s,
                          &t[mode][0]);
         if (st >= 0) st = time_ms([&]() { return do_blurT(P, P->t, P->w, s, taps); }, reps, s, &t[mode][1]);
+        P->taps_tall = false;
         if (st < 0) {
             P->blur_fft = keep[0];
             P->blur_fft_taps = keep[1];
             return st;
         }
     }
-    // the taps are at most as fast as the matrix cores
+    // The matrix cores round as little as the grid, the chain of p^2 taps up to four
+    // times as much (Gaussian PSF, p = 31: 5.2e-7 and 1.2e-7 of A^T's 2-norm, p = 17: 2.9
+    // and 1.1).  So the taps take the grid's place only where they are 1.3 times as
+    // fast with the tiles of large images; on the 8-row tiles alone they did so for
+    // many explicit restorations of small images, whose error grew two- to fourfold
+    // (192 x 192, p = 31: 2.5e-7 -> 1.0e-6).  The grid also where the matrix cores lose
+    // to it: the taps are not faster than they.
     const double fft = have_fft == MLBA_OK ? t[1][0] + t[1][1] : 1e300;
     P->blur_fft = fft < t[0][0] + t[0][1] ? 1 : 0;
-    P->blur_fft_taps = P->blur_fft || fft < t[2][0] + t[2][1] ? 1 : 0;
+    P->blur_fft_taps = P->blur_fft || fft < 1.3 * (t[3][0] + t[3][1]) ? 1 : 0;
     for (int i = 0; i < 2; ++i) P->taps_ms[i] = t[2][i];
     if (ms_out)
         for (int i = 0; i < 4; ++i) ms_out[i] = t[i / 2][i % 2];

@@ -33,6 +33,7 @@ struct mlba_plan_s {
     int blur_fft = 0;          // A and A^T by FFTs of an M x M grid
     int blur_fft_taps = 0;     // the same choice where the direct blur keeps the order of the taps
     double taps_ms[2] = {-1.0, -1.0};  // that blur's A and A^T in the last mlba_plan_autotune
+    bool taps_tall = false;            // that blur without its tiles for small images (mlba_plan_autotune)
     mlba::FftConv fc{};        // its plan and buffers (allocated on first use)
     float* psf = nullptr;
     uint4* taps[2] = {nullptr, nullptr};  // split taps of the direct A^T and A

@@ -241,14 +241,17 @@ static hipError_t launch_tap(const ConvJob& j, int flip, double* partials, int* 
     return hipGetLastError();
 }
 
+bool tapconv_small(int D, int p) { return p <= 33 && tap_tiles(D, tap_ty(1, 8)) < 128; }
+
 // Output tile: two columns a thread (8-row tiles) while 32-row tiles would
 // leave most of the chip idle (at 226 x 226 and p = 31, 116 workgroups instead
 // of 32); two rows a thread (64-row tiles, fewer LDS reads per multiply-add)
 // unless that tiling leaves a nearly empty second round of workgroups; else
 // one.
 template <int P>
-static hipError_t launch_tap_side(const ConvJob& j, int flip, double* partials, int* n_partials, hipStream_t s) {
-    if (tap_tiles(j.D, tap_ty(1, 8)) < 128) return launch_tap<P, 1, 2>(j, flip, partials, n_partials, s);
+static hipError_t launch_tap_side(const ConvJob& j, int flip, double* partials, int* n_partials, hipStream_t s,
+                                  bool tall) {
+    if (!tall && tapconv_small(j.D, P)) return launch_tap<P, 1, 2>(j, flip, partials, n_partials, s);
     const long t2 = tap_tiles(j.D, tap_ty(2, 8));
     const int lds2 = tap_lds_floats(P, tap_ty(2, 8)) * 4;
     const long slots = 256L * (160 * 1024 / lds2);
@@ -261,11 +264,12 @@ int tapconv_partials_count(int D) { return tap_tiles(D, tap_ty(1, 2)); }  // upp
 
 static size_t tap_generic_lds(int p) { return (size_t)(tap_lds_floats(p, TAP_GENERIC_TY) + p * p) * sizeof(float); }
 
-hipError_t launch_tapconv(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s) {
+hipError_t launch_tapconv(const ConvJob& j, int p, int flip, double* partials, int* n_partials, hipStream_t s,
+                          bool tall) {
     switch (p) {
 #define MLBA_TAP_CASE(PP) \
     case PP:              \
-        return launch_tap_side<PP>(j, flip, partials, n_partials, s);
+        return launch_tap_side<PP>(j, flip, partials, n_partials, s, tall);
         MLBA_TAP_SIDES(MLBA_TAP_CASE)
 #undef MLBA_TAP_CASE
         default: {
