@@ -1124,6 +1124,10 @@ int mlba_plan_autotune(mlba_plan_t P, int reps, double* ms_out, hipStream_t s) {
     HIPCHK(launch_fill_hash(P->t, (size_t)P->n * P->n, 2u, s));
     for (int mode = 0; mode < 4; ++mode) {
         if (mode == 1 && have_fft != MLBA_OK) continue;
+        if (mode == 3 && !tapconv_small(P->n, P->p)) {  // the same launches as mode 2
+            for (int i = 0; i < 2; ++i) t[3][i] = t[2][i];
+            continue;
+        }
         const bool taps = mode >= 2;
         P->blur_fft = mode == 1;
         P->taps_tall = mode == 3;
